@@ -20,7 +20,8 @@
 // are the same for every lane, so they sit in LDS and every read is a
 // broadcast. For q > 1 a box that only one member reaches (on any lane and
 // sample of the chunk) adds that member's own extent product; the other
-// subset terms are exact zeros. Samples are processed in chunks held in registers and each box
+// subset terms are exact zeros. Samples are processed in chunks held in
+// registers and each box
 // is read once per chunk, which leaves a branch-free VALU loop of
 // 2m + (m-1) + 1 ops per (sample, box) for q = 1. No cross-lane reduction is
 // needed: a lane owns all S x boxes terms of its candidate.
@@ -31,6 +32,11 @@
 #include "bo_internal.h"
 
 namespace bo {
+
+size_t ehvi_lds_bytes(int S, int q, int m, int nbox) {
+  return sizeof(float) * ((size_t)S * q * m + (size_t)nbox * 2 * m);
+}
+
 namespace {
 
 constexpr int kThreads = 256;
@@ -48,15 +54,32 @@ __device__ __forceinline__ float mask_infeasible(const float (&y)[MO], const Ehv
   return ok ? y[0] : -__builtin_inff();
 }
 
+// q = 1. The samples fall into kGroups groups of whole chunks of SC, each
+// group's terms are summed on their own and the group sums added in group
+// order, so the result does not depend on how the groups are spread: W waves
+// (a power of two, blockDim.x = 64 max(W, 4)) share 64 candidates, each taking
+// kGroups / W consecutive groups, and meet in LDS. Bound by vector issue when
+// the chip is full (W = 1); a small batch has too few candidates for that
+// (8192 are 128 waves on 1024 SIMDs), and its time is one lane's serial walk
+// over its samples, which W divides. One wave per candidate set against the
+// rule of q1_waves (m = 2): M = 4096, S = 128: 22.2 -> 5.1 us; M = 8192,
+// S = 512: 78.4 -> 9.2 us; M = 65536, S = 256: 58.7 -> 26.9 us; M = 1048576,
+// S = 512 (W = 1 either way): 326 and 319 us.
+constexpr int kGroups = 16;
 template <int MO, int SC, bool CONS>
-__global__ __launch_bounds__(kThreads) void k_ehvi_q1(EhviArgs a) {
+__global__ __launch_bounds__(1024) void k_ehvi_q1(EhviArgs a, int W) {
   extern __shared__ float sm[];
   float* zs = sm;                                   // [S][MO]
   float* bx = sm + a.S * MO;                        // [nbox][2*MO]
-  for (int i = threadIdx.x; i < a.S * MO; i += kThreads) zs[i] = a.Z[i];
-  for (int i = threadIdx.x; i < a.nbox * 2 * MO; i += kThreads) bx[i] = a.boxes[i];
+  float* part = bx + a.nbox * 2 * MO;               // W > 1: [64 max(W, 4) / (64 W)][kGroups][64]
+  const int nt = blockDim.x;
+  for (int i = threadIdx.x; i < a.S * MO; i += nt) zs[i] = a.Z[i];
+  for (int i = threadIdx.x; i < a.nbox * 2 * MO; i += nt) bx[i] = a.boxes[i];
   __syncthreads();
-  const int64_t b = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sub = wave / W, ws = wave % W;          // candidate set of this wave, its share
+  const int64_t b = ((int64_t)blockIdx.x * (nt / 64 / W) + sub) * 64 + lane;
   const bool valid = b < a.nbat;
   float mu[MO], sd[MO];
   bool nan_in = false;      // a NaN posterior gives a NaN acquisition
@@ -66,39 +89,59 @@ __global__ __launch_bounds__(kThreads) void k_ehvi_q1(EhviArgs a) {
     sd[k] = valid ? a.sd[b * a.sd_ps + k * a.sd_ks] : 0.f;
     nan_in = nan_in || (mu[k] != mu[k]) || (sd[k] != sd[k]);
   }
-  float acc = 0.f;
-  for (int s0 = 0; s0 < a.S; s0 += SC) {
-    float y[SC][MO];
+  const int gs = (a.S + kGroups * SC - 1) / (kGroups * SC) * SC;   // samples per group
+  float tot = 0.f;
+  for (int g = ws * (kGroups / W); g < (ws + 1) * (kGroups / W); ++g) {
+    float acc = 0.f;
+    for (int s0 = g * gs; s0 < min(a.S, (g + 1) * gs); s0 += SC) {
+      float y[SC][MO];
 #pragma unroll
-    for (int j = 0; j < SC; ++j)
+      for (int j = 0; j < SC; ++j)
 #pragma unroll
-      for (int k = 0; k < MO; ++k) {
-        const int s = s0 + j;
-        const int sl = (s < a.S) ? s : (a.S - 1);
-        // samples past S get -inf: every extent clamps to 0
-        y[j][k] = (s < a.S) ? fmaf(sd[k], zs[sl * MO + k], mu[k]) : -__builtin_inff();
+        for (int k = 0; k < MO; ++k) {
+          const int s = s0 + j;
+          const int sl = (s < a.S) ? s : (a.S - 1);
+          // samples past S get -inf: every extent clamps to 0
+          y[j][k] = (s < a.S) ? fmaf(sd[k], zs[sl * MO + k], mu[k]) : -__builtin_inff();
+        }
+      if constexpr (CONS) {
+#pragma unroll
+        for (int j = 0; j < SC; ++j) y[j][0] = mask_infeasible<MO>(y[j], a);
       }
-    if constexpr (CONS) {
+      for (int c = 0; c < a.nbox; ++c) {
+        float lo[MO], w[MO];
 #pragma unroll
-      for (int j = 0; j < SC; ++j) y[j][0] = mask_infeasible<MO>(y[j], a);
+        for (int k = 0; k < MO; ++k) {
+          lo[k] = bx[c * 2 * MO + k];
+          w[k] = bx[c * 2 * MO + MO + k];
+        }
+#pragma unroll
+        for (int j = 0; j < SC; ++j) {
+          float t = clamp_ext(y[j][0], lo[0], w[0]);
+#pragma unroll
+          for (int k = 1; k < MO; ++k) t *= clamp_ext(y[j][k], lo[k], w[k]);
+          acc += t;
+        }
+      }
     }
-    for (int c = 0; c < a.nbox; ++c) {
-      float lo[MO], w[MO];
-#pragma unroll
-      for (int k = 0; k < MO; ++k) {
-        lo[k] = bx[c * 2 * MO + k];
-        w[k] = bx[c * 2 * MO + MO + k];
-      }
-#pragma unroll
-      for (int j = 0; j < SC; ++j) {
-        float t = clamp_ext(y[j][0], lo[0], w[0]);
-#pragma unroll
-        for (int k = 1; k < MO; ++k) t *= clamp_ext(y[j][k], lo[k], w[k]);
-        acc += t;
-      }
-    }
+    if (W == 1) tot += acc;
+    else part[(sub * kGroups + g) * 64 + lane] = acc;
   }
-  if (valid) a.ehvi[b] = nan_in ? __builtin_nanf("") : acc / static_cast<float>(a.S);
+  if (W > 1) {
+    __syncthreads();
+    if (ws != 0) return;
+    for (int g = 0; g < kGroups; ++g) tot += part[(sub * kGroups + g) * 64 + lane];
+  }
+  if (valid) a.ehvi[b] = nan_in ? __builtin_nanf("") : tot / static_cast<float>(a.S);
+}
+
+// Waves per 64 candidates at q = 1: the fewest that give the chip's 1024
+// SIMDs four waves each, at most one per sample group.
+int q1_waves(int64_t nbat) {
+  const int64_t sets = (nbat + 63) / 64;
+  int W = 1;
+  while (W < kGroups && sets * W < 4096) W *= 2;
+  return W;
 }
 
 // q-batch version: lane owns a batch of Q points; y_s[a][k] is sampled with
@@ -264,36 +307,41 @@ __global__ __launch_bounds__(kThreads) void k_ehvi_q(EhviArgs a) {
 
 // Launch with the dynamic-LDS limit raised for that kernel (set on every
 // launch, so that it holds on whichever device is current).
-template <typename K>
-hipError_t launch_k(K kern, unsigned grid, size_t lds, hipStream_t st, const EhviArgs& a) {
+template <typename K, typename... A>
+hipError_t launch_k(K kern, unsigned grid, unsigned threads, size_t lds, hipStream_t st, A... a) {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, a);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), lds, st, a...);
   return hipGetLastError();
 }
 
 template <int MO, bool CONS>
 hipError_t launch_mo(const EhviArgs& a, hipStream_t st) {
-  // q = 1: a lane per candidate; q > 1: a workgroup per 64 batches
-  const int per = (a.q == 1) ? kThreads : 64;
-  const unsigned grid = static_cast<unsigned>((a.nbat + per - 1) / per);
-  // (q > 1: at least the waves' partial sums, which reuse the space at the end)
-  const size_t lds = sizeof(float) * std::max<size_t>((size_t)a.S * a.q * MO + (size_t)a.nbox * 2 * MO,
-                                                      a.q > 1 ? kThreads : 0);
+  const size_t lds = ehvi_lds_bytes(a.S, a.q, MO, a.nbox);
+  if (a.q == 1) {
+    // the group sums of W > 1 waves come after the boxes; where they do not
+    // fit (thousands of samples and boxes) one wave takes all the groups
+    int W = q1_waves(a.nbat);
+    const size_t part = sizeof(float) * kGroups * 64 * (W < 4 ? 4 / W : 1);
+    if (lds + part > 160 * 1024) W = 1;
+    const int per = 64 * (W < 4 ? 4 / W : 1);       // candidates per workgroup
+    const unsigned grid = static_cast<unsigned>((a.nbat + per - 1) / per);
+    return launch_k(&k_ehvi_q1<MO, 16, CONS>, grid, 64 * std::max(W, 4), lds + (W > 1 ? part : 0),
+                    st, a, W);
+  }
+  // q > 1: a workgroup per 64 batches (LDS: at least the waves' partial sums,
+  // which reuse the space at the end)
+  const unsigned grid = static_cast<unsigned>((a.nbat + 63) / 64);
+  const size_t ldsq = std::max<size_t>(lds, sizeof(float) * kThreads);
   switch (a.q) {
-    case 1: return launch_k(&k_ehvi_q1<MO, 16, CONS>, grid, lds, st, a);
-    case 2: return launch_k(&k_ehvi_q<MO, 2, 4, CONS>, grid, lds, st, a);
-    case 4: return launch_k(&k_ehvi_q<MO, 4, 2, CONS>, grid, lds, st, a);
+    case 2: return launch_k(&k_ehvi_q<MO, 2, 4, CONS>, grid, kThreads, ldsq, st, a);
+    case 4: return launch_k(&k_ehvi_q<MO, 4, 2, CONS>, grid, kThreads, ldsq, st, a);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
-
-size_t ehvi_lds_bytes(int S, int q, int m, int nbox) {
-  return sizeof(float) * ((size_t)S * q * m + (size_t)nbox * 2 * m);
-}
 
 hipError_t launch_ehvi(const EhviArgs& a, hipStream_t st) {
   if (a.nbat <= 0) return hipSuccess;

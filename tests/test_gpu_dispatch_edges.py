@@ -1,0 +1,43 @@
+"""GPU tests of the launch rules' edges: sizes either side of each line."""
+import numpy as np
+import pytest
+
+import bo_inputs as bi
+import oracle as O
+from gpu_util import TOL_EHVI, gpu_run, oracle_ehvi_given, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _announce(*a):
+    print("[case]", *a, flush=True)
+
+
+@pytest.mark.parametrize("m,S", [(2, 1), (2, 15), (2, 17), (2, 255), (3, 257), (2, 4096)])
+def test_single_point_ehvi_sample_groups(m, S):
+    """q = 1: the samples' groups (remainders, empty groups) and the waves that
+    share them. A candidate's value depends neither on the batch it is in nor
+    on how many waves share its samples: the prefixes take 16, 8, 4, 2 and 1
+    waves per 64 candidates. The first rows are checked against the oracle's
+    boxes on the GPU's own posterior: sums of at most 4096 fp32 products whose
+    factors carry a few units of 2^-24, far inside the parity bar."""
+    wl = bi.make_config(0, seed=3, M=262145)
+    if m == 3:
+        y3 = (-np.sum(wl.X.astype(np.float64) ** 2, axis=1) / wl.d).astype(np.float32)
+        wl.Y = np.concatenate([wl.Y, y3[:, None]], axis=1)
+        wl.m = 3
+        for f in ("lengthscale", "outputscale", "noise"):
+            v = getattr(wl, f)
+            setattr(wl, f, np.concatenate([v, v[:1]]))
+        wl.ref = np.append(wl.ref, wl.Y[:, 2].min() - np.float32(0.1)).astype(np.float32)
+    wl.Z = np.random.default_rng(S).standard_normal((S, 1, m)).astype(np.float32)
+    full = gpu_run(wl)["ehvi"]
+    for M in (1, 63, 65, 16384, 16385, 32769, 65537, 131073):
+        _announce("ehvi groups", m, S, M)
+        part = gpu_run(wl, cand=wl.cand[:M], want_musd=False)["ehvi"]
+        np.testing.assert_array_equal(part, full[:M])
+    g = gpu_run(wl, cand=wl.cand[:200])
+    front = O.pareto_front(wl.Y.astype(np.float64), wl.ref.astype(np.float64))
+    lo, hi = O.box_decomposition(wl.Y[front].astype(np.float64), wl.ref.astype(np.float64))
+    want = oracle_ehvi_given(g["mu"], g["sigma"], wl.Z, {"lo": lo, "hi": hi})
+    np.testing.assert_allclose(g["ehvi"], want, rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
