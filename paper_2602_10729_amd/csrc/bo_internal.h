@@ -82,7 +82,7 @@ struct Model {
   double* ils64 = nullptr;       // [m][d]
   int n_fit = 0;
   uint16_t* xf = nullptr;        // [m][nb][dist_frags(dx)][512] distance fragments of X
-  float* x2 = nullptr;           // [m][2][n_pad] squared norms of the centred rows
+  float* x2 = nullptr;           // [m][2][n_pad] squared norms of the centred rows (plain: halved)
   float* ctr = nullptr;          // [m][dx] centre of the scaled coordinates
 
   // scoring workspace (grown on demand)
@@ -183,10 +183,19 @@ hipError_t launch_scale_x(const float* X, int64_t n, int d, int m, int nb, int d
 // Squared distances in the posterior kernel come from the expansion
 // |c|^2 + |x|^2 - 2 c.x of centred scaled coordinates, with c.x on the fp16
 // matrix cores: each value splits into hi = fp16(v) and lo = fp16(2^11 (v -
-// hi)); one accumulator takes sum x_hi c_hi over the D = dx slots (stream 0),
-// another sum x_lo c_hi + x_hi c_lo over 2D positions (stream 1), and c.x =
-// acc0 + 2^-11 acc1. Fragments of 32 k-positions per 16-row group: stream 0
-// first, then stream 1.
+// hi)); stream 0 pairs x_hi with c_hi over the D = dx slots, stream 1 x_lo
+// with c_hi and x_hi with c_lo over 2D positions. Fragments of 32 k-positions
+// per 16-row group: stream 0 first, then stream 1.
+// Plain models accumulate h = r^2 / 2 in one chain that starts from
+// (|c|^2 + |x|^2) / 2, the candidate's halves negated, and stream 1's high
+// halves (x's and c's) scaled by 2^-11 so that its terms have stream 0's
+// scale: half as many vector operations per pair as two accumulators. The
+// scaled halves may be fp16 subnormals; what they lose is below
+// 2^-26 (|c| + |x|), and pairs with r^2 < 1 are recomputed exactly.
+// Composite models keep two accumulators, c.x = acc0 + 2^-11 acc1, unscaled
+// halves and whole norms: the one-chain form was 3% faster there too, but it
+// moves the means by 1e-6, and under feasibility thresholds a sample that
+// changes side moves an acquisition value by up to 5% of their rms.
 __host__ __device__ constexpr int dist_frags0(int dx) { return (dx + 31) / 32; }
 __host__ __device__ constexpr int dist_frags(int dx) { return (dx + 31) / 32 + (2 * dx + 31) / 32; }
 constexpr float kDistLoScale = 2048.0f;
@@ -194,7 +203,7 @@ constexpr float kDistLoScale = 2048.0f;
 // Centre the scaled coordinates (ctr = mean over the n rows), then write the
 // A fragments of the centred rows (xf, zero for rows past n) and their
 // squared norms per coordinate group (x2 [2][n_pad]: routing slots t < 4*dr4,
-// then the rest; a plain model has everything in the second group).
+// then the rest; a plain model has everything, halved, in the second group).
 hipError_t launch_pack_x(const float* Xs, int64_t n, int m, int nb, int dx, int dr4,
                          float* ctr, uint16_t* xf, float* x2, hipStream_t st);
 
@@ -277,7 +286,7 @@ struct NehviMeansArgs {
   const float* invls;      // [m][dx]
   const uint16_t* xf;      // [m][xf_stride] centred-X distance fragments (fp16 bits)
   int64_t xf_stride;
-  const float* x2;         // [m][2][n_pad] squared norms of the centred rows per group
+  const float* x2;         // [m][2][n_pad] squared norms of the centred rows per group (plain: halved)
   const float* ctr;        // [m][dx] centre of the scaled coordinates
   const uint16_t* Gp;      // packed G^T fragments (fp16 bits)
   float s[3];              // output scales (composite: of the routing term)
@@ -344,7 +353,7 @@ struct PosteriorArgs {
   // split scale 2^(14 - E) (s = f 2^E, f in [0.5, 1)), and 2^(E - 14)
   float ss, kinv0;
   const uint16_t* xf;  // [nb][dist_frags(dx)][512] centred-X distance fragments
-  const float* x2;     // [2][n_pad] squared norms of the centred rows per coordinate group
+  const float* x2;     // [2][n_pad] squared norms of the centred rows per coordinate group (plain: halved)
   const float* ctr;    // [dx] centre subtracted from the scaled coordinates
   int n, nb;
   float s;             // output scale (composite: of the routing term)

@@ -775,11 +775,11 @@ __global__ __launch_bounds__(256) void k_center_x(const float* __restrict__ Xs, 
 // the A fragment of v_mfma_f32_16x16x32_f16 that lane l supplies (row 16g +
 // l%16, positions 8(l/16) .. +7 of the fragment's 32), from the centred row
 // xc = Xs - ctr: stream 0 holds hi(xc[p]) at p < dx, stream 1 lo(xc[p]) at
-// p < dx and hi(xc[p - dx]) at dx <= p < 2dx; zero elsewhere and for rows
-// past n.
+// p < dx and hi1 hi(xc[p - dx]) at dx <= p < 2dx (hi1 = 1 for composite
+// models, else 2^-11: dist_frags); zero elsewhere and for rows past n.
 __global__ __launch_bounds__(256) void k_pack_x(const float* __restrict__ Xs, int64_t n,
                                                 int n_pad, int nb, int dx,
-                                                const float* __restrict__ ctr,
+                                                const float* __restrict__ ctr, float hi1,
                                                 _Float16* __restrict__ xf) {
   const int k = blockIdx.y;
   const int nf = dist_frags(dx), f0 = dist_frags0(dx);
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(256) void k_pack_x(const float* __restrict__ Xs, in
         const _Float16 h = static_cast<_Float16>(xc);
         v = static_cast<_Float16>((xc - static_cast<float>(h)) * kDistLoScale);
       } else if (p < 2 * dx) {
-        v = static_cast<_Float16>(x[p - dx] - c[p - dx]);
+        v = static_cast<_Float16>(x[p - dx] - c[p - dx]) * static_cast<_Float16>(hi1);
       }
     }
     dst[e] = v;
@@ -811,7 +811,8 @@ __global__ __launch_bounds__(256) void k_pack_x(const float* __restrict__ Xs, in
 }
 
 // x2[k][0][i] = sum over routing slots (t < 4*dr4) of (Xs - ctr)^2, x2[k][1][i]
-// over the others, both fp32 in slot order; zero for rows past n
+// over the others (half of it for a plain model, dr4 = 0), both fp32 in slot
+// order; zero for rows past n
 __global__ __launch_bounds__(256) void k_norm_x(const float* __restrict__ Xs, int64_t n,
                                                 int n_pad, int dx, int dr4,
                                                 const float* __restrict__ ctr,
@@ -830,7 +831,7 @@ __global__ __launch_bounds__(256) void k_norm_x(const float* __restrict__ Xs, in
     }
   }
   x2[((int64_t)k * 2 + 0) * n_pad + i] = g0;
-  x2[((int64_t)k * 2 + 1) * n_pad + i] = g1;
+  x2[((int64_t)k * 2 + 1) * n_pad + i] = (dr4 > 0) ? g1 : 0.5f * g1;
 }
 
 // ---- log marginal likelihood and its gradient ------------------------------
@@ -1164,7 +1165,8 @@ hipError_t launch_pack_x(const float* Xs, int64_t n, int m, int nb, int dx, int 
   hipLaunchKernelGGL(k_center_x, dim3(dx, m), dim3(256), 0, st, Xs, n, n_pad, dx, ctr);
   const int64_t th = (int64_t)nb * dist_frags(dx) * 64;
   hipLaunchKernelGGL(k_pack_x, dim3(static_cast<unsigned>((th + 255) / 256), m), dim3(256), 0, st,
-                     Xs, n, n_pad, nb, dx, ctr, reinterpret_cast<_Float16*>(xf));
+                     Xs, n, n_pad, nb, dx, ctr, dr4 > 0 ? 1.0f : 1.0f / kDistLoScale,
+                     reinterpret_cast<_Float16*>(xf));
   hipLaunchKernelGGL(k_norm_x, dim3(static_cast<unsigned>((n_pad + 255) / 256), m), dim3(256), 0,
                      st, Xs, n, n_pad, dx, dr4, ctr, x2);
   return hipGetLastError();

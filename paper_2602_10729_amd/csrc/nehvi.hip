@@ -461,6 +461,7 @@ __device__ __forceinline__ void lds_sync() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Matern correlations of a squared scaled distance (composite kernel).
 __device__ __forceinline__ float m32(float r2) {
   const float r = __builtin_amdgcn_sqrtf(r2);
   constexpr float kNegSqrt3Log2e = static_cast<float>(-1.73205080756887729353 * 1.44269504088896340736);
@@ -472,6 +473,15 @@ __device__ __forceinline__ float m52(float r2, float s) {
   constexpr float kNegSqrt5Log2e = static_cast<float>(-2.23606797749978969641 * 1.44269504088896340736);
   const float e = __builtin_amdgcn_exp2f(kNegSqrt5Log2e * r);
   return s * fmaf(r, 2.23606798f, fmaf(r2, 1.66666667f, 1.0f)) * e;
+}
+
+// Matern-5/2 from half the squared scaled distance h = r^2 / 2, u = sqrt(h):
+// s (1 + sqrt10 u + 10/3 h) exp(-sqrt10 u), su = s sqrt10, sh = s 10/3.
+constexpr float kM52u = 3.16227766f, kM52h = 3.33333333f;
+__device__ __forceinline__ float m52h(float h, float s, float su, float sh) {
+  const float u = __builtin_amdgcn_sqrtf(h);
+  constexpr float kNegSqrt10Log2e = static_cast<float>(-3.16227766016837933200 * 1.44269504088896340736);
+  return fmaf(u, su, fmaf(h, sh, s)) * __builtin_amdgcn_exp2f(kNegSqrt10Log2e * u);
 }
 
 constexpr int kMW = 8;                 // waves per workgroup
@@ -502,8 +512,8 @@ template <int DX4, int CB, bool COMP>
 __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
   constexpr int RS = 4 * DX4;
   constexpr int NS = COMP ? 2 : 1;
-  constexpr int F0 = dist_frags0(RS), NF = dist_frags(RS);
-  static_assert(F0 == 1 && NF <= 3, "at most 32 coordinate slots");
+  constexpr int NF = dist_frags(RS);
+  static_assert(dist_frags0(RS) == 1 && NF <= 3, "at most 32 coordinate slots");
   static_assert(2 * kMT * 96 <= 3 * kRingSlot, "candidate fragments fit the ring");
   __shared__ __align__(16) _Float16 ring[3 * kRingSlot];
   __shared__ __align__(16) float ctile[kMT * RS];   // exact scaled candidates
@@ -578,7 +588,7 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
         const bool in = !COMP || ((t < 4 * a.dr4) == (g == 0));
         if (in) n2 = fmaf(ct[t], ct[t], n2);
       }
-      c2[g] = n2;
+      c2[g] = COMP ? n2 : 0.5f * n2;
     }
     if (half == 0 && (lane >> 4) == 0) {
 #pragma unroll
@@ -593,9 +603,10 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
           const _Float16 hi = static_cast<_Float16>(in ? ct[t] : 0.f);
           const _Float16 lo = static_cast<_Float16>(
               in ? (ct[t] - static_cast<float>(static_cast<_Float16>(ct[t]))) * kDistLoScale : 0.f);
-          v[t / 8][t % 8] = hi;
-          v[(32 + t) / 8][(32 + t) % 8] = hi;
-          v[(32 + RS + t) / 8][(32 + RS + t) % 8] = lo;
+          v[t / 8][t % 8] = COMP ? hi : -hi;
+          v[(32 + t) / 8][(32 + t) % 8] =
+              COMP ? hi : -hi * static_cast<_Float16>(1.0f / kDistLoScale);
+          v[(32 + RS + t) / 8][(32 + RS + t) % 8] = COMP ? lo : -lo;
         }
 #pragma unroll
         for (int i = 0; i < 12; ++i) *reinterpret_cast<halfx8*>(h + 8 * i) = v[i];
@@ -630,34 +641,51 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
     if constexpr (COMP) wtv = __builtin_bit_cast(floatx4, ld4(w_rs, row * 4, 0));
   };
   auto produce = [&](int jb) {
-    floatx4 d0[NS], d1[NS];
-#pragma unroll
-    for (int g = 0; g < NS; ++g) {
-      d0[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-      d1[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int f = 0; f < F0; ++f)
-        d0[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f], cb[g][f], d0[g], 0, 0, 0);
-#pragma unroll
-      for (int f = F0; f < NF; ++f)
-        d1[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f], cb[g][f], d1[g], 0, 0, 0);
-    }
-    float r2[NS][4];
+    float dist[NS][4];
     bool ex[4];
     bool any = false;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float rt = 0.f, nt = 0.f;
+    if constexpr (COMP) {
+      constexpr int F0 = dist_frags0(RS);
+      floatx4 d0[NS], d1[NS];
 #pragma unroll
       for (int g = 0; g < NS; ++g) {
-        const float nrm = c2[g] + x2v[g][e];
-        const float dot = fmaf(d1[g][e], 1.0f / kDistLoScale, d0[g][e]);
-        r2[g][e] = fmaxf(fmaf(-2.0f, dot, nrm), 0.f);
-        rt += r2[g][e];
-        nt += nrm;
+        d0[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+        d1[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int f = 0; f < F0; ++f)
+          d0[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f], cb[g][f], d0[g], 0, 0, 0);
+#pragma unroll
+        for (int f = F0; f < NF; ++f)
+          d1[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f], cb[g][f], d1[g], 0, 0, 0);
       }
-      ex[e] = rt < fmaf(nt, 1.0f / 256.0f, 1.0f);
-      any = any || ex[e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float rt = 0.f, nt = 0.f;
+#pragma unroll
+        for (int g = 0; g < NS; ++g) {
+          const float nrm = c2[g] + x2v[g][e];
+          const float dot = fmaf(d1[g][e], 1.0f / kDistLoScale, d0[g][e]);
+          dist[g][e] = fmaxf(fmaf(-2.0f, dot, nrm), 0.f);
+          rt += dist[g][e];
+          nt += nrm;
+        }
+        ex[e] = rt < fmaf(nt, 1.0f / 256.0f, 1.0f);
+        any = any || ex[e];
+      }
+    } else {
+      floatx4 dd;
+      float hn[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dd[e] = hn[e] = c2[0] + x2v[0][e];
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        dd = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f], cb[0][f], dd, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        dist[0][e] = dd[e];
+        ex[e] = !(dd[e] >= fmaf(hn[e], 1.0f / 256.0f, 0.5f));
+        any = any || ex[e];
+      }
     }
     if (__builtin_amdgcn_ballot_w64(any) != 0) {
       // exact differences for the pairs that need them (rows past n_pad read
@@ -681,32 +709,33 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
           else s1 += t;
         }
         if (ex[e]) {
-          if constexpr (COMP) {
-            r2[0][e] = s0;
-            r2[1][e] = s1;
-          } else {
-            r2[0][e] = s1;
-          }
+          dist[0][e] = COMP ? s0 : 0.5f * s1;
+          if constexpr (COMP) dist[NS - 1][e] = s1;
         }
       }
     }
     halfx4 hi, lo;
+    float kvs[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float kv;
       if constexpr (COMP) {
-        const float k5 = m52(r2[0][e], 1.0f);
-        const float k3 = m32(r2[1][e]);
+        const float k5 = m52(dist[0][e], 1.0f);
+        const float k3 = m32(dist[NS - 1][e]);
         kv = fmaf(wsd * wtv[e], k3, k5 * fmaf(sints, k3, sks));
       } else {
-        kv = m52(r2[0][e], sks);
+        kv = m52h(dist[0][e], sks, sks * kM52u, sks * kM52h);
       }
       // one fp32 value for both halves (the compiler may otherwise fuse the
       // last product into the fp16 conversions and derive the high half twice)
       asm volatile("" : "+v"(kv));
-      const _Float16 h = static_cast<_Float16>(kv);
-      hi[e] = h;
-      lo[e] = static_cast<_Float16>(kv - static_cast<float>(h));
+      kvs[e] = kv;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      hi[e] = static_cast<_Float16>(kvs[e]);
+      // kv - hi, exact: one mixed-precision FMA
+      lo[e] = static_cast<_Float16>(fmaf(static_cast<float>(hi[e]), -1.0f, kvs[e]));
     }
     _Float16* dst = ring + (jb % 3) * kRingSlot + col * kKS + rq;
     *reinterpret_cast<halfx4*>(dst) = hi;

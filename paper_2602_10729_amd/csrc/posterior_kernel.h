@@ -40,11 +40,11 @@
 // in the same 4-lane group and are exchanged with DPP quad permutes) are
 // kept.
 //
-// K*^T is produced two blocks ahead of its use into an LDS ring of 16
+// K*^T is produced kG + 1 blocks ahead of its use into an LDS ring of 16
 // blocks (512 rows) of fp16 hi/lo planes, from the training rows' distance
 // fragments, norms and alpha, which each lane loads one step ahead into
 // registers. While the matrix cores work on block J, the waves form the
-// squared distances of block J + 2 with a few more MFMAs (the expansion
+// squared distances of block J + kG + 1 with a few more MFMAs (the expansion
 // |c|^2 + |x|^2 - 2c.x over centred coordinates, exact differences for pairs
 // near a training point, see Producer), evaluate the ARD Matern-5/2 values on
 // the vector ALUs and accumulate mu = K* alpha in fp32.
@@ -53,7 +53,20 @@
 // The kernel evaluations and the MFMAs of a step are independent and are
 // interleaved, so each SIMD's matrix core and vector ALU work together as far
 // as their shared issue allows.
-// One barrier per step publishes the produced block.
+// One barrier per kG = 4 steps publishes the produced blocks, and the steps
+// after the last production have none: the waves drift apart by up to four
+// steps, one's kernel values beside the other's MFMAs, and the triangle's last
+// rounds, uneven over the waves step by step, even out over the pass. With a
+// barrier per step a wave idled 800 of each step's 2570 cycles behind its
+// SIMD's other wave. 5.61e7 -> 5.26e7 GRBM cycles per headline launch
+// (1,048,576 points, n = 1024, d = 16); 2 and 8 steps measured the same as 4.
+// What bounds the launch is the chip's power: those 6% of cycles gave 2.9% of
+// time (the clock went from 2.11 to 2.04 GHz), and the launch issues 1.06-1.09
+// PFLOP/s against the 1.13 a large library fp16 matrix product reaches on the
+// same card. So operations taken out count more than stalls: the one-chain
+// distances, the folded output scale and the mixed-precision low halves (76 ->
+// 44 vector instructions per producing step and wave) gave another 1.5%.
+// 3.32-3.35 -> 3.19-3.21 ms in all.
 //
 // Each wave owns RB row-block slots, slot r holding row block
 // base + 8r + (r even ? wave : 7 - wave); this snake keeps the per-SIMD
@@ -89,6 +102,7 @@ constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kJ = 32;                      // rows of K*^T per step (MFMA k)
 constexpr int kRing = 16;                   // K*^T blocks held in LDS
+constexpr int kG = 4;                       // steps per barrier while producing
 constexpr int kCSH = kRing * kJ + 8;        // ring column stride in halves (260 dwords)
 
 __device__ __forceinline__ float matern52_f(float r2, float s) {
@@ -108,6 +122,15 @@ __device__ __forceinline__ float matern32_f(float r2) {
   return fmaf(r, 1.73205081f, 1.0f) * __builtin_amdgcn_exp2f(kNegSqrt3Log2e * r);
 }
 
+// Matern-5/2 from half the squared scaled distance h = r^2 / 2, u = sqrt(h):
+// s (1 + sqrt10 u + 10/3 h) exp(-sqrt10 u), with su = s sqrt10 and
+// sh = s 10/3 given.
+constexpr float kM52u = 3.16227766f, kM52h = 3.33333333f;
+__device__ __forceinline__ float matern52_h(float h, float s, float su, float sh) {
+  constexpr float kNegSqrt10Log2e = static_cast<float>(-3.16227766016837933200 * 1.44269504088896340736);
+  const float u = __builtin_amdgcn_sqrtf(h);
+  return fmaf(u, su, fmaf(h, sh, s)) * __builtin_amdgcn_exp2f(kNegSqrt10Log2e * u);
+}
 __device__ __forceinline__ float quad_xor(float v, int x) {
   // DPP quad_perm: lane i of each group of 4 reads lane i ^ x.
   int iv = __float_as_int(v);
@@ -149,14 +172,16 @@ typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
 //
 // Squared distances: r^2 = |c|^2 + |x|^2 - 2 c.x over coordinates centred on
 // the training mean, c.x on the matrix cores from fp16 hi and 2^11-scaled lo
-// halves (the fit packs the rows, the kernel the candidates; two accumulator
-// streams, see dist_frags). Where the expansion can cancel badly, i.e. for a
-// pair whose approximate r^2 is below 1 + (|c|^2 + |x|^2)/256, the pair is
-// recomputed from exact differences of the scaled coordinates: near a
-// training point k(x*, x_i) is close to its maximum and sigma^2 cancels,
-// elsewhere the expansion's error (about 2^-20 (|c|^2 + |x|^2)) changes sigma
-// by far less than its fp32 rounding. The choice is made per pair, so a
-// point's result does not depend on its neighbours in the tile.
+// halves (the fit packs the rows, the kernel the candidates; see dist_frags).
+// A plain model's chain of MFMAs starts from (|c|^2 + |x|^2) / 2 and leaves
+// h = r^2 / 2, which the Matern evaluation takes as it is. Where the expansion
+// can cancel badly, i.e. for a pair whose approximate r^2 is below
+// 1 + (|c|^2 + |x|^2)/256, the pair is recomputed from exact differences of
+// the scaled coordinates: near a training point k(x*, x_i) is close to its
+// maximum and sigma^2 cancels, elsewhere the expansion's error (about
+// 2^-20 (|c|^2 + |x|^2)) changes sigma by far less than its fp32 rounding.
+// The choice is made per pair, so a point's result does not depend on its
+// neighbours in the tile.
 // Composite kernel: one expansion per coordinate group (routing slots first,
 // then deployment), the candidate fragments masked to the group; the test
 // above uses the total over both groups.
@@ -198,42 +223,70 @@ __device__ __forceinline__ void prod_load(Producer<NT, DX4, COMP>& P, int n_pad,
   if constexpr (COMP) P.wt = __builtin_bit_cast(floatx4, load4(P.wt_rs, row * 4, 0));
 }
 
-// Squared scaled distances of this lane's four rows of block jb (operands
-// loaded by prod_load). ctile: the tile's exact scaled candidate coordinates
-// [NT][D]. Reads the operands' distance part only (xa, x2).
+// Squared scaled distances of this lane's four rows of the block whose
+// operands prod_load fetched, by the expansion: dist[0] = r^2 / 2 (plain) or
+// the groups' r^2 (composite). ex marks the pairs to recompute exactly, any
+// whether there is one. Reads the operands' distance part only (xa, x2).
 template <int NT, int DX4, bool COMP>
-__device__ __forceinline__ void produce_dist(Producer<NT, DX4, COMP>& P, const PosteriorArgs& a, int jb,
-                                             const float* ctile, float (&r2)[Producer<NT, DX4, COMP>::NS][4]) {
+__device__ __forceinline__ void produce_dist(const Producer<NT, DX4, COMP>& P,
+                                             float (&dist)[Producer<NT, DX4, COMP>::NS][4],
+                                             bool (&ex)[4], bool& any) {
   using Pr = Producer<NT, DX4, COMP>;
-  constexpr int NS = Pr::NS, F0 = Pr::F0, NF = Pr::NF;
-  floatx4 d0[NS], d1[NS];
-#pragma unroll
-  for (int g = 0; g < NS; ++g) {
-    d0[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-    d1[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int f = 0; f < F0; ++f)
-      d0[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(P.xa[f], P.cb[g][f], d0[g], 0, 0, 0);
-#pragma unroll
-    for (int f = F0; f < NF; ++f)
-      d1[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(P.xa[f], P.cb[g][f], d1[g], 0, 0, 0);
-  }
-  bool ex[4];
-  bool any = false;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    float rt = 0.f, nt = 0.f;
+  constexpr int NS = Pr::NS, NF = Pr::NF;
+  any = false;
+  if constexpr (COMP) {
+    constexpr int F0 = Pr::F0;
+    floatx4 d0[NS], d1[NS];
 #pragma unroll
     for (int g = 0; g < NS; ++g) {
-      const float nrm = P.c2[g] + P.x2[g][e];
-      const float dot = fmaf(d1[g][e], 1.0f / kDistLoScale, d0[g][e]);
-      r2[g][e] = fmaxf(fmaf(-2.0f, dot, nrm), 0.f);
-      rt += r2[g][e];
-      nt += nrm;
+      d0[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+      d1[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int f = 0; f < F0; ++f)
+        d0[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(P.xa[f], P.cb[g][f], d0[g], 0, 0, 0);
+#pragma unroll
+      for (int f = F0; f < NF; ++f)
+        d1[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(P.xa[f], P.cb[g][f], d1[g], 0, 0, 0);
     }
-    ex[e] = rt < fmaf(nt, 1.0f / 256.0f, 1.0f);
-    any = any || ex[e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float rt = 0.f, nt = 0.f;
+#pragma unroll
+      for (int g = 0; g < NS; ++g) {
+        const float nrm = P.c2[g] + P.x2[g][e];
+        const float dot = fmaf(d1[g][e], 1.0f / kDistLoScale, d0[g][e]);
+        dist[g][e] = fmaxf(fmaf(-2.0f, dot, nrm), 0.f);
+        rt += dist[g][e];
+        nt += nrm;
+      }
+      ex[e] = rt < fmaf(nt, 1.0f / 256.0f, 1.0f);
+      any = any || ex[e];
+    }
+  } else {
+    floatx4 d;
+    float hn[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) d[e] = hn[e] = P.c2[0] + P.x2[0][e];
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+      d = __builtin_amdgcn_mfma_f32_16x16x32_f16(P.xa[f], P.cb[0][f], d, 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      dist[0][e] = d[e];
+      // (a NaN, from fp16 overflow, is near too)
+      ex[e] = !(d[e] >= fmaf(hn[e], 1.0f / 256.0f, 0.5f));
+      any = any || ex[e];
+    }
   }
+}
+
+// The exact distances of the pairs marked in ex (any: this lane has one) of
+// block jb. ctile: the tile's exact scaled candidate coordinates [NT][D].
+template <int NT, int DX4, bool COMP>
+__device__ __forceinline__ void exact_dist(Producer<NT, DX4, COMP>& P, const PosteriorArgs& a, int jb,
+                                           const float* ctile, float (&dist)[Producer<NT, DX4, COMP>::NS][4],
+                                           const bool (&ex)[4], bool any) {
+  using Pr = Producer<NT, DX4, COMP>;
   if (__builtin_amdgcn_ballot_w64(any) != 0) {
     // exact differences for the pairs that need them (rows past n_pad read
     // zero coordinates)
@@ -255,12 +308,8 @@ __device__ __forceinline__ void produce_dist(Producer<NT, DX4, COMP>& P, const P
         else s1 += t;
       }
       if (ex[e]) {
-        if constexpr (COMP) {
-          r2[0][e] = s0;
-          r2[1][e] = s1;
-        } else {
-          r2[0][e] = s1;
-        }
+        dist[0][e] = COMP ? s0 : 0.5f * s1;
+        if constexpr (COMP) dist[Pr::NS - 1][e] = s1;
       }
     }
   }
@@ -271,9 +320,10 @@ __device__ __forceinline__ void produce_dist(Producer<NT, DX4, COMP>& P, const P
 // planes; adds them into mu.
 template <int NT, int DX4, bool COMP>
 __device__ __forceinline__ void produce_kv(Producer<NT, DX4, COMP>& P, const PosteriorArgs& a, int jb,
-                                           const float (&r2)[Producer<NT, DX4, COMP>::NS][4],
+                                           const float (&dist)[Producer<NT, DX4, COMP>::NS][4],
                                            const floatx4& al, const floatx4& wt, _Float16* ring) {
   halfx4 hi, lo;
+  float kvs[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     // no mask: rows past n meet zero columns of L^{-1} and zero alpha;
@@ -283,11 +333,11 @@ __device__ __forceinline__ void produce_kv(Producer<NT, DX4, COMP>& P, const Pos
     float kv;
     if constexpr (COMP) {
       // s_route M52(r_route) + s_dep w* w_i M32(r_dep) + s_int M52 M32
-      const float k5 = matern52_f(r2[0][e], 1.0f);
-      const float k3 = matern32_f(r2[1][e]);
+      const float k5 = matern52_f(dist[0][e], 1.0f);
+      const float k3 = matern32_f(dist[1][e]);
       kv = fmaf(P.wsd * wt[e], k3, k5 * fmaf(P.sis, k3, P.ss));
     } else {
-      kv = matern52_f(r2[0][e], a.ss);
+      kv = matern52_h(dist[0][e], a.ss, a.ss * kM52u, a.ss * kM52h);
     }
     // kv is rounded to fp32 here, once: otherwise the compiler may fuse its
     // last product into the fp16 conversions and derive the high half twice
@@ -297,11 +347,15 @@ __device__ __forceinline__ void produce_kv(Producer<NT, DX4, COMP>& P, const Pos
     // pin the loads and LDS accesses around it.)
     asm("" : "+v"(kv));
     P.mu = fmaf(al[e], kv, P.mu);
-    const _Float16 h = static_cast<_Float16>(kv);
-    hi[e] = h;
-    lo[e] = static_cast<_Float16>(kv - static_cast<float>(h));
+    kvs[e] = kv;
   }
-  _Float16* dst = ring + P.col * kCSH + (jb % kRing) * kJ + P.rq;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    hi[e] = static_cast<_Float16>(kvs[e]);
+    // kv - hi, exact: one mixed-precision FMA
+    lo[e] = static_cast<_Float16>(fmaf(static_cast<float>(hi[e]), -1.0f, kvs[e]));
+  }
+  _Float16* dst = ring + P.col * kCSH + (jb & (kRing - 1)) * kJ + P.rq;
   *reinterpret_cast<halfx4*>(dst) = hi;
   *reinterpret_cast<halfx4*>(dst + NT * kCSH) = lo;
 }
@@ -310,9 +364,11 @@ __device__ __forceinline__ void produce_kv(Producer<NT, DX4, COMP>& P, const Pos
 template <int NT, int DX4, bool COMP>
 __device__ __forceinline__ void produce(Producer<NT, DX4, COMP>& P, const PosteriorArgs& a, int jb,
                                         const float* ctile, _Float16* ring) {
-  float r2[Producer<NT, DX4, COMP>::NS][4];
-  produce_dist(P, a, jb, ctile, r2);
-  produce_kv(P, a, jb, r2, P.al, P.wt, ring);
+  float dist[Producer<NT, DX4, COMP>::NS][4];
+  bool ex[4], any;
+  produce_dist(P, dist, ex, any);
+  exact_dist(P, a, jb, ctile, dist, ex, any);
+  produce_kv(P, a, jb, dist, P.al, P.wt, ring);
 }
 
 // Row block of slot r in the pass starting at row block `base`.
@@ -380,7 +436,7 @@ struct Ctx {
   __amdgpu_buffer_rsrc_t lp_rs;   // packed fragments of this objective
   int nb, nbj, zero_blk, n_pad, wave, tid;
   int poff;                 // the block produced at step J is J + poff (this pass)
-  int pw0, pw1;             // the pass's production window: blocks [pw0, pw1)
+  int bar1;                 // chunk ends before step bar1 have a barrier
   int voff;                 // this lane's byte offset inside a fragment plane
   const _Float16* Kb;       // this lane's B-fragment base inside the ring
   const float* ctile;       // the tile's exact scaled candidate coordinates [NT][D]
@@ -390,7 +446,7 @@ struct Ctx {
 // 8*(lane/16) .. +7.
 template <int NT>
 __device__ __forceinline__ void load_b(const Ctx& C, int J, int h, BHalf& B) {
-  const _Float16* kb = C.Kb + (J % kRing) * kJ;
+  const _Float16* kb = C.Kb + (J & (kRing - 1)) * kJ;
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     B.hi[b] = *reinterpret_cast<const halfx8*>(kb + (2 * h + b) * 16 * kCSH);
@@ -402,10 +458,13 @@ __device__ __forceinline__ void load_b(const Ctx& C, int J, int h, BHalf& B) {
 // fragments on entry (read during the previous step) and the first half of
 // block J + 1's on exit; the second half is read at the start. The MFMAs of
 // block J (fragments for J + 1 requested on the way) and the producer's block
-// J + 2 (when PROD) are independent and are left to the scheduler to
-// interleave: the fp16 MFMAs overlap the VALU work. The step's barrier
-// publishes the produced block; block J + 1 was
-// published by the previous step's, so its B fragments can be read early.
+// J + poff (when PROD) are independent and are left to the scheduler to
+// interleave: the fp16 MFMAs overlap the VALU work. A barrier ends the step
+// that ends a chunk of kG steps while blocks are being produced (bar1). Block
+// J + 1 was published at least a chunk end earlier (poff > kG), so its B
+// fragments can be read early; the slot that block J + poff goes to held block
+// J + poff - 16, which every wave left before the last chunk end
+// (poff <= 16 - kG).
 template <int LO, int RB, int NT, int DX4, bool COMP, bool PROD>
 __device__ __forceinline__ void step(const Ctx& C, const PosteriorArgs& a, Producer<NT, DX4, COMP>& P,
                                      _Float16* ring, const Slots<RB>& sl, int J,
@@ -416,24 +475,24 @@ __device__ __forceinline__ void step(const Ctx& C, const PosteriorArgs& a, Produ
   load_b<NT>(C, J, 1, B1);
   // the distances consume the producer's operands, except alpha and the
   // weights (copied), so the next block's are requested right after them, a
-  // whole step before they are needed (requested at the end of the step,
-  // they made the next step start by waiting for them)
+  // whole step before they are needed and ahead of the step's fragment loads
+  // on every path: loads return in order, so behind the fragments their wait
+  // would be a wait for those too
   using Pr = Producer<NT, DX4, COMP>;
-  float r2[Pr::NS][4];
+  float dist[Pr::NS][4];
   floatx4 al, wt;
   if constexpr (PROD) {
-    produce_dist(P, a, J + C.poff, C.ctile, r2);
+    bool ex[4], any;
+    produce_dist(P, dist, ex, any);
+    exact_dist(P, a, J + C.poff, C.ctile, dist, ex, any);
     al = P.al;
     wt = P.wt;
   }
   if constexpr (PROD) {
     prod_load(P, C.n_pad, J + 1 + C.poff, C.tid & 63);
-  } else {
-    // only the step before the first producing one needs them
-    const int jn = J + 1 + C.poff;
-    if (jn >= C.pw0 && jn < C.pw1) prod_load(P, C.n_pad, jn, C.tid & 63);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  if constexpr (PROD) produce_kv(P, a, J + C.poff, r2, al, wt, ring);
+  if constexpr (PROD) produce_kv(P, a, J + C.poff, dist, al, wt, ring);
   // slot pairs in turn, each pair's fragments for J + 1 requested as soon as
   // its MFMAs are issued (about half a step before the next step needs them);
   // the next block's first B half is read once the last pair is done with it
@@ -451,7 +510,7 @@ __device__ __forceinline__ void step(const Ctx& C, const PosteriorArgs& a, Produ
     // interleave: the scheduler otherwise runs the producer's VALU work and
     // the MFMAs as two separate stretches, and the two waves of a SIMD
     // (kept in step by the barriers) then contend for the same unit
-    constexpr int nM = 3 * NCB * (RB - LO) + Pr::NS * Pr::NF;
+    constexpr int nM = 3 * NCB * (RB - LO);
     constexpr int nV = 4 * (COMP ? 40 : 22);
     if constexpr (nM > 0) {
 #pragma unroll
@@ -462,17 +521,17 @@ __device__ __forceinline__ void step(const Ctx& C, const PosteriorArgs& a, Produ
     }
   }
   __builtin_amdgcn_sched_barrier(0);
-  lds_barrier();
+  if ((J & (kG - 1)) == kG - 1 && J < C.bar1) lds_barrier();
 }
 
-// Steps [j0, j1) for slots [LO, RB); the producer runs at the steps whose
-// block J + poff lies in the pass's production window [pw0, pw1).
+// Steps [j0, j1) for slots [LO, RB); the producer runs at the steps in
+// [ps0, ps1).
 template <int LO, int RB, int NT, int DX4, bool COMP>
 __device__ __forceinline__ void span(const Ctx& C, const PosteriorArgs& a, Producer<NT, DX4, COMP>& P,
                                      _Float16* ring, const Slots<RB>& sl, int j0,
-                                     int j1, int pw0, int pw1, BHalf& B0, AFrag (&av)[RB],
+                                     int j1, int ps0, int ps1, BHalf& B0, AFrag (&av)[RB],
                                      floatx4 (&acc)[RB][NT / 16]) {
-  const int p0 = min(max(pw0 - C.poff, j0), j1), p1 = min(max(pw1 - C.poff, p0), j1);
+  const int p0 = min(max(ps0, j0), j1), p1 = min(max(ps1, p0), j1);
   int J = j0;
   for (; J < p0; ++J) step<LO, RB, NT, DX4, COMP, false>(C, a, P, ring, sl, J, B0, av, acc);
   for (; J < p1; ++J) step<LO, RB, NT, DX4, COMP, true>(C, a, P, ring, sl, J, B0, av, acc);
@@ -485,16 +544,16 @@ __device__ __forceinline__ void span(const Ctx& C, const PosteriorArgs& a, Produ
 template <int R, int RB, int NT, int DX4, bool COMP>
 __device__ __forceinline__ void rounds(const Ctx& C, const PosteriorArgs& a, Producer<NT, DX4, COMP>& P,
                                        _Float16* ring, const Slots<RB>& sl,
-                                       int base, int pw0, int pw1, BHalf& B0, AFrag (&av)[RB],
+                                       int base, int ps0, int ps1, BHalf& B0, AFrag (&av)[RB],
                                        floatx4 (&acc)[RB][NT / 16]) {
   if constexpr (R < RB) {
     const int j0 = base / 2 + 4 * R;
     if (j0 >= C.nbj) return;
     const int jend = min(j0 + 4, C.nbj);
     const int jlive = min(slot_block(base, R, C.wave) / 2 + 1, jend);
-    span<R, RB, NT, DX4, COMP>(C, a, P, ring, sl, j0, jlive, pw0, pw1, B0, av, acc);
-    span<R + 1, RB, NT, DX4, COMP>(C, a, P, ring, sl, jlive, jend, pw0, pw1, B0, av, acc);
-    rounds<R + 1, RB, NT, DX4, COMP>(C, a, P, ring, sl, base, pw0, pw1, B0, av, acc);
+    span<R, RB, NT, DX4, COMP>(C, a, P, ring, sl, j0, jlive, ps0, ps1, B0, av, acc);
+    span<R + 1, RB, NT, DX4, COMP>(C, a, P, ring, sl, jlive, jend, ps0, ps1, B0, av, acc);
+    rounds<R + 1, RB, NT, DX4, COMP>(C, a, P, ring, sl, base, ps0, ps1, B0, av, acc);
   }
 }
 
@@ -573,7 +632,7 @@ __global__ __launch_bounds__(kThreads) void k_posterior(PosteriorArgs a) {
         const bool in = !COMP || ((t < 4 * a.dr4) == (g == 0));
         if (in) n2 = fmaf(ct[t], ct[t], n2);
       }
-      P.c2[g] = n2;
+      P.c2[g] = COMP ? n2 : 0.5f * n2;
     }
     // a candidate with a non-finite coordinate: its unscale factor is NaN, so
     // its mu and variance read NaN (the hot loop's clamps would hide it)
@@ -592,9 +651,10 @@ __global__ __launch_bounds__(kThreads) void k_posterior(PosteriorArgs a) {
           const _Float16 hi = static_cast<_Float16>(in ? ct[t] : 0.f);
           const _Float16 lo = static_cast<_Float16>(
               in ? (ct[t] - static_cast<float>(static_cast<_Float16>(ct[t]))) * kDistLoScale : 0.f);
-          v[t / 8][t % 8] = hi;
-          v[(32 + t) / 8][(32 + t) % 8] = hi;
-          v[(32 + D + t) / 8][(32 + D + t) % 8] = lo;
+          v[t / 8][t % 8] = COMP ? hi : -hi;
+          v[(32 + t) / 8][(32 + t) % 8] =
+              COMP ? hi : -hi * static_cast<_Float16>(1.0f / kDistLoScale);
+          v[(32 + D + t) / 8][(32 + D + t) % 8] = COMP ? lo : -lo;
         }
 #pragma unroll
         for (int i = 0; i < 12; ++i) *reinterpret_cast<halfx8*>(h + 8 * i) = v[i];
@@ -707,36 +767,42 @@ __global__ __launch_bounds__(kThreads) void k_posterior(PosteriorArgs a) {
       sl.last[r] = I < a.nb ? I / 2 : -1;
       scv[r] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
           C.lp_rs, 4 * min(I, a.nb) + 0 * lane, (C.zero_blk + 1) * 2048, 0));
-      av[r] = load_a(C.lp_rs, C.voff, frag_block(sl.first[r], sl.last[r], 0, C.zero_blk));
     }
-    // Production schedule. Starting over, blocks 0 and 1 are made here and
-    // block J + 2 at step J (poff = 2). A pass that finds blocks 0..have-1
-    // in the ring makes block have - 1 + J at step J >= 1 (poff = have - 1),
-    // into the slot of block J - 1, which no wave reads after step J - 1:
-    // the new blocks are made during the pass's first steps, where every
-    // slot is live and the matrix cores have the most work to hide them
-    // behind. The operands of a block are loaded a step before it is made.
-    const int have0 = have;
+    // Production schedule. Starting over, the first kG + 1 blocks are made
+    // here and block J + kG + 1 at step J. A pass that finds blocks 0 .. 15 in
+    // the ring makes block J + 16 - kG at step J >= kG, into the slot of block
+    // J - kG, which no wave reads after the chunk before: the new blocks are
+    // made during the pass's first steps, where every slot is live and the
+    // matrix cores have the most work to hide them behind. The operands of a
+    // block are loaded a step before it is made.
+    int ps0 = 0;
     if (have == 0) {
-      // start over: blocks 0 and 1, and mu from scratch
+      if (base > 0) lds_barrier();   // the last pass's readers are done
+      // start over: the first blocks, and mu from scratch
       P.mu = 0.f;
+      C.poff = kG + 1;
       prod_load(P, n_pad, 0, lane);
-      produce(P, a, 0, ctile, ring);
-      prod_load(P, n_pad, 1, lane);
-      produce(P, a, 1, ctile, ring);
-      have = 2;
+      for (int jb = 0; jb < min(kG + 1, jpass); ++jb) {
+        produce(P, a, jb, ctile, ring);
+        prod_load(P, n_pad, jb + 1, lane);
+      }
       lds_barrier();
+    } else {
+      C.poff = kRing - kG;
+      ps0 = kG;
+      prod_load(P, n_pad, kRing, lane);
     }
-    C.poff = have0 ? have0 - 1 : 2;
-    prod_load(P, n_pad, C.poff, lane);   // block poff: made at step 0 when new
-    const int pw0 = have, pw1 = jpass;   // blocks this pass produces
-    C.pw0 = pw0;
-    C.pw1 = pw1;
+    const int ps1 = max(jpass - C.poff, 0);
+    C.bar1 = (ps1 > ps0) ? ps1 + kG - 1 : 0;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < RB; ++r)
+      av[r] = load_a(C.lp_rs, C.voff, frag_block(sl.first[r], sl.last[r], 0, C.zero_blk));
     BHalf B0;
     load_b<NT>(C, 0, 0, B0);
     // blocks left of this pass's triangle: every slot is live
-    span<0, RB, NT, DX4, COMP>(C, a, P, ring, sl, 0, base / 2, pw0, pw1, B0, av, acc);
-    rounds<0, RB, NT, DX4, COMP>(C, a, P, ring, sl, base, pw0, pw1, B0, av, acc);
+    span<0, RB, NT, DX4, COMP>(C, a, P, ring, sl, 0, base / 2, ps0, ps1, B0, av, acc);
+    rounds<0, RB, NT, DX4, COMP>(C, a, P, ring, sl, base, ps0, ps1, B0, av, acc);
     have = (jpass <= kRing) ? max(have, jpass) : 0;
 
     // undo the row-block scale of L^{-1} (the column scale of K*^T is undone

@@ -41,3 +41,23 @@ def test_single_point_ehvi_sample_groups(m, S):
     lo, hi = O.box_decomposition(wl.Y[front].astype(np.float64), wl.ref.astype(np.float64))
     want = oracle_ehvi_given(g["mu"], g["sigma"], wl.Z, {"lo": lo, "hi": hi})
     np.testing.assert_allclose(g["ehvi"], want, rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
+
+
+@pytest.mark.parametrize("cfg,n", [(2, n) for n in (1, 17, 129, 160, 161, 192, 256, 257, 511, 513, 545,
+                                                    639, 641, 1024)] +
+                         [(4, n) for n in (1025, 1057, 1537, 2047)])
+def test_posterior_block_counts(cfg, n):
+    """Observation counts either side of the posterior's chunk, pass and ring
+    lines (32-row blocks: 5 are made before the first step, chunks of 4, passes
+    of 16, two 128-row slots up to 256 rows), two tiles and a remainder."""
+    from gpu_util import TOL_MU, TOL_SIGMA, oracle_fit, oracle_score
+    wl = bi.make_config(cfg, seed=5, M=130 if cfg == 2 else 33)
+    wl.X, wl.Y, wl.n = wl.X[:n].copy(), wl.Y[:n].copy(), n
+    wl.Z = wl.Z[:16].copy()
+    for comp in (None, bi.composite_hyperparameters(wl)):
+        _announce("posterior blocks", cfg, n, comp is not None)
+        g = gpu_run(wl, comp=comp)
+        o = oracle_score(oracle_fit(wl, comp), wl)
+        np.testing.assert_allclose(g["mu"], o["mu"], rtol=TOL_MU[0], atol=TOL_MU[1])
+        np.testing.assert_allclose(g["sigma"], o["sigma"], rtol=TOL_SIGMA[0], atol=TOL_SIGMA[1])
+        np.testing.assert_allclose(g["ehvi"], o["ehvi"], rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
