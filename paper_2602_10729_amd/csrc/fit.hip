@@ -24,8 +24,8 @@
 //           workgroup that updates the next diagonal tile factors and
 //           inverts it at once, so no separate factor launch is needed after
 //           the first.
-// Two launches per block column; the serial chain is one 64-step fused
-// factor and inverse of the diagonal block per block column.
+// Two launches per block column; the serial chain is one factor and inverse
+// of a diagonal block (64 pivots in one wave) per block column.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -133,109 +133,181 @@ __global__ __launch_bounds__(256) void k_weights(const float* __restrict__ X, in
   wts[(int64_t)k * n_pad + i] = w;
 }
 
-// 1 / sqrt(d), d > 0: the hardware estimate refined by two Newton steps
-// y <- y (3 - d y^2) / 2, each of which roughly squares the relative error.
+// 1 / sqrt(d), d > 0: the hardware estimate y (relative error below 2^-24,
+// measured) and one third-order step in e = 1 - d y^2, whose own error is
+// about e^3 / 3; within 2^-52.7, measured over 2^20 values in [2^-40, 2^21].
 __device__ __forceinline__ double rsqrt_d(double d) {
-  double y = __builtin_amdgcn_rsq(d);
-  const double h = 0.5 * d;
-  y = y * fma(-h * y, y, 1.5);
-  return y * fma(-h * y, y, 1.5);
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-(d * y), y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ double readlane_d(double v, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(u), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), lane);
+  return __builtin_bit_cast(double, (static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// Sixteen pivots in one wave: lane l holds a row of sixteen columns, lanes
+// 0..15 the rows of the (symmetric, lower part used) diagonal block. On return
+// the diagonal lanes hold their rows of L (entries past the diagonal are
+// meaningless) and every other lane its row times L^{-T}: a row of the panel
+// below, or, started from an identity row, a row of L^{-T} itself. Returns
+// whether a pivot was not positive and finite (every row is then zero but for
+// a one at column lane % 16, so that nothing non-finite goes on).
+//
+// Columns stay unscaled until the end (r[c] -= r[j] / p_j * A_cj), so A_cj at
+// the rows to come goes to all lanes through scalar registers while 1 / p_j is
+// still being formed, and a pivot's chain is a lane read, the reciprocal (the
+// estimate and one third-order step, three multiply-adds, within 2^-53),
+// a product and one multiply-add. The updates of the pivot before fill its
+// gaps: they are dealt out between the chain's links, which the scheduler, left
+// to itself, puts after all of them. The pivots are gathered into lanes 0..15,
+// so one reciprocal square root serves all sixteen.
+__device__ __forceinline__ bool panel16(double (&r)[16]) {
+  const int l = threadIdx.x & 63;
+  double dv = 1.0;
+  double s[16], m = 0.0;         // A_c,j-1 at the rows to come; r[j-1] / p_(j-1)
+#pragma unroll
+  for (int c = 0; c < 16; ++c) s[c] = 0.0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    // column j is up to date; columns j + 1 .. still lack pivot j - 1
+    const int n = (j > 0) ? 15 - j : 0;
+    auto fill = [&](int q) {     // quarter q of them
+#pragma unroll
+      for (int i = q * n / 4; i < (q + 1) * n / 4; ++i) r[j + 1 + i] = fma(-m, s[j + 1 + i], r[j + 1 + i]);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    const double p = readlane_d(r[j], j);
+    const double y = __builtin_amdgcn_rcp(p);
+    fill(0);
+    const double e = fma(-p, y, 1.0);
+    fill(1);
+    const double t = fma(e, e, e);
+    fill(2);
+    const double id = fma(y, t, y);
+    fill(3);
+#pragma unroll
+    for (int c = j + 1; c < 16; ++c) s[c] = readlane_d(r[j], c);
+    m = r[j] * id;
+    if (j < 15) r[j + 1] = fma(-m, s[j + 1], r[j + 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    dv = (l == j) ? p : dv;      // lane j: pivot j
+  }
+  const bool bad_any = __builtin_amdgcn_ballot_w64(l < 16 && (!(dv > 0.0) || !isfinite(dv))) != 0;
+  const double is = rsqrt_d(dv);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) r[j] *= readlane_d(is, j);
+  if (bad_any) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) r[j] = ((l & 15) == j) ? 1.0 : 0.0;
+  }
+  return bad_any;
+}
+
+// dst = base - P Q or P Q (16x16 blocks, dst's and P's row stride LDP) on the
+// fp64 matrix cores (the operand and result lanes of gemm_nt_64):
+// A[i][k] = P[i LDP + k], B[k][j] = Q[k qk + j qj]. SUB subtracts the product
+// from dst, or from zero when `fresh`. dst may be Q: it is read first.
+template <bool SUB>
+__device__ __forceinline__ void block16(double* dst, const double* P, const double* Q, int qk,
+                                        int qj, bool fresh) {
+  const int l = threadIdx.x & 63, i = l & 15, k = l >> 4;
+  doublex4 c0 = {}, c1 = {};
+  double pa[4], qb[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    pa[t] = P[i * LDP + 4 * t + k];
+    qb[t] = Q[(4 * t + k) * qk + i * qj];
+  }
+  if (SUB) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c0[e] = fresh ? 0.0 : dst[(k + 4 * e) * LDP + i];
+  }
+#pragma unroll
+  for (int t = 0; t < 4; t += 2) {
+    c0 = __builtin_amdgcn_mfma_f64_16x16x4f64(SUB ? -pa[t] : pa[t], qb[t], c0, 0, 0, 0);
+    c1 = __builtin_amdgcn_mfma_f64_16x16x4f64(SUB ? -pa[t + 1] : pa[t + 1], qb[t + 1], c1, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) dst[(k + 4 * e) * LDP + i] = c0[e] + c1[e];
 }
 
 // Factor the symmetric 64x64 block held in LDS `a` (lower triangle read) and
-// invert the factor: on return a = L (zeros above the diagonal) and
-// x = L^{-1} (zeros above the diagonal). All eight waves of the 512-thread
-// workgroup take part (every thread must call this), two per SIMD so that
-// one wave's multiply-adds fill the other's wait on the pivot chain: thread
-// (w, c) = (wave, lane) keeps, in registers indexed only by unrolled
-// constants,
-//   row c of A, columns 8w .. 8w+7, and
-//   column c of X, rows 8w .. 8w+7.
+// invert the factor: on return a = L and x = L^{-1} in their lower triangles
+// (what lies above is unspecified: store_lower). Every thread of the
+// 512-thread workgroup must call this.
 //
-// The factor (right-looking, unscaled) and the inverse (forward
-// substitution, one column of X per lane) advance together, one barrier per
-// step j; only the wave holding column j of A and row j of X writes:
-//   before the barrier it publishes column j of A as it stands
-//   (A_ij = L_ij L_jj for rows i > j, zeros for rows <= j; one write of the
-//   whole wave), the pivot A_jj, and row j of X as it stands (X_jc L_jj);
-//   the buffers are double-buffered by step parity;
-//   after it, every thread takes 1 / L_jj = A_jj^{-1/2} and updates
-//     A_ic -= A_ij A_cj / A_jj   (its row i, its 8 columns c)
-//     X_ic -= A_ij (X_jc L_jj) / A_jj   (its column c, its 8 rows i);
-//   the zeros of the published column leave rows and columns <= j as they
-//   are (above the diagonal A is never read again; rows of X up to j are
-//   final).
-// Row j of X keeps the factor L_jj until the end, where every row of X and
-// every column of A is scaled by its 1 / L_jj.
-// A non-positive or non-finite pivot sets *flag and is replaced by 1.
-// Scratch: scr holds 6 x 64 doubles, 16-byte aligned (two published columns
-// of A, two published rows of X, two pivots, the 64 values 1 / L_jj).
+// Right-looking over four panels of 16 columns. Period p:
+//   A: wave 0 factors the panel (panel16, a lane per row), wave 1 the same
+//      diagonal block beside sixteen identity rows, which leaves its inverse
+//      D_p without a wait for wave 0; the waves 2 + j carry the inverse on by
+//      period q = p - 1, one column of 16x16 blocks each: X_qj = D_q R_qj, then
+//      R_ij -= L_iq X_qj below (R starts as the identity; its blocks live in x);
+//   B: the trailing blocks A_ij -= L_ip L_jp^T, a wave each.
+// A barrier ends each part. Bound by the serial chain of the 64 pivots, about
+// 175 cycles each in one wave's registers; eight waves with a barrier and an
+// LDS round trip per pivot took 650. 64x64 block in LDS: 41.5e3 -> 21.5e3
+// cycles; k_factor_first (one block) 21.5 -> 11.7 us, k_update at n = 1024,
+// m = 2 25.2 -> 16.6 us, at n = 2048, m = 3 38.4 -> 30.0 us.
 constexpr int kFactorThreads = 512;
-__device__ __forceinline__ void chol_inv64(double (*a)[LDP], double (*x)[LDP], double* scr,
-                                           int* flag) {
-  const int c = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // column group 8w ..
-  double* colbuf = scr;                      // [2][64] column j of A, rows > j
-  double* rowbuf = scr + 2 * B;              // [2][64] row j of X
-  double* pivbuf = scr + 4 * B;              // [2]     A_jj
-  double* rdiag = scr + 5 * B;               // [64]    1 / L_jj
-  double r[8], xv[8];
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    r[t] = a[c][8 * w + t];
-    xv[t] = (8 * w + t == c) ? 1.0 : 0.0;
-  }
-  bool bad_any = false;
-  // steps j = 8 jw + jt: the group of the pivot is a loop variable and the
-  // position within it an unrolled constant (register indices stay constant
-  // while the straight-line code stays one group long)
+__device__ __forceinline__ void chol_inv64(double (*a)[LDP], double (*x)[LDP], int* flag) {
+  const int l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll 1
-  for (int jw = 0; jw < 8; ++jw) {
+  for (int p = 0; p < 4; ++p) {
+    const int o = 16 * p;
+    double r[16];
+    if (w < 2) {
+      // wave 0: rows o + l (those past the block repeat others, unused);
+      // wave 1: the diagonal block's rows, then identity rows
+      const int row = (w == 0) ? o + l : o + (l & 15);
 #pragma unroll
-  for (int jt = 0; jt < 8; ++jt) {
-    const int j = 8 * jw + jt;
-    double* col = colbuf + (jt & 1) * B;
-    double* row = rowbuf + (jt & 1) * B;
-    if (w == jw) {
-      col[c] = (c > j) ? r[jt] : 0.0;       // A_cj of this lane's row c
-      row[c] = xv[jt];                      // X_jc before its division by L_jj
-      if (c == j) pivbuf[jt & 1] = r[jt];
+      for (int c = 0; c < 16; ++c) r[c] = a[row & (B - 1)][o + c];
+      if (w == 1 && l >= 16) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) r[c] = (c == (l & 15)) ? 1.0 : 0.0;
+      }
+      const bool bad = panel16(r);
+      if (w == 0) {
+        if (bad && l == 0) atomicOr(flag, 1);
+        if (l >= 16 && row < B) {
+#pragma unroll
+          for (int c = 0; c < 16; ++c) a[row][o + c] = r[c];
+        }
+      } else if (l >= 16 && l < 32) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) x[o + c][o + (l & 15)] = r[c];
+      }
+    } else if (w - 2 < p) {
+      const int q = 16 * (p - 1), j = 16 * (w - 2);
+      if (j < q) block16<false>(&x[q][j], &x[q][q], &x[q][j], LDP, 1, false);
+      for (int i = q + 16; i < B; i += 16)
+        block16<true>(&x[i][j], &a[i][q], &x[q][j], LDP, 1, j == q);
     }
     __syncthreads();
-    // every read of the step is issued together, ahead of the arithmetic
-    const double a_jj = pivbuf[jt & 1];
-    const double a_cj = col[c];
-    const double x_jc = row[c];
-    double2 l[4];
+    // wave 0 has read the diagonal block by now: L_pp's rows
+    if (w == 1 && l < 16) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) l[t] = *reinterpret_cast<const double2*>(col + 8 * w + 2 * t);
-    __builtin_amdgcn_sched_barrier(0);
-    const bool bad = !(a_jj > 0.0) || !isfinite(a_jj);
-    const double d = bad ? 1.0 : a_jj;
-    bad_any = bad_any || bad;
-    const double isd = rsqrt_d(d);
-    const double id = isd * isd;
-    const double mrow = a_cj * id;          // A_cj / A_jj for this lane's row c
-    const double xs = x_jc * id;            // (X_jc / L_jj) / L_jj
-#pragma unroll
-    for (int t = 0; t < 8; t += 2) {
-      r[t] = fma(-mrow, l[t / 2].x, r[t]);
-      r[t + 1] = fma(-mrow, l[t / 2].y, r[t + 1]);
-      xv[t] = fma(-l[t / 2].x, xs, xv[t]);
-      xv[t + 1] = fma(-l[t / 2].y, xs, xv[t + 1]);
+      for (int c = 0; c < 16; ++c) a[o + l][o + c] = r[c];
     }
-    if (threadIdx.x == 0) rdiag[j] = isd;
+    if (p < 3) {
+      // trailing block w: (i, j) in the order (1,1) (2,1) (2,2) (3,1) ..
+      const int i = w < 1 ? 1 : w < 3 ? 2 : 3, j = w - i * (i - 1) / 2 + 1;
+      if (i <= 3 - p && w < 6) {
+        const int ib = o + 16 * i, jb = o + 16 * j;
+        block16<true>(&a[ib][jb], &a[ib][o], &a[jb][o], 1, LDP, false);
+      }
+    } else if (w >= 2 && w < 5) {
+      const int j = 16 * (w - 2);
+      block16<false>(&x[o][j], &x[o][o], &x[o][j], LDP, 1, false);
+    }
+    __syncthreads();
   }
-  }
-  if (bad_any && threadIdx.x == 0) atomicOr(flag, 1);   // every thread saw every pivot
-  __syncthreads();   // rdiag is complete; every published read is done
-#pragma unroll
-  for (int t = 0; t < 8; ++t) {
-    const int k = 8 * w + t;                // column of A / row of X
-    a[c][k] = (c >= k) ? r[t] * rdiag[k] : 0.0;
-    x[k][c] = xv[t] * rdiag[k];
-  }
-  __syncthreads();
 }
 
 // Copies of 64x64 tiles between global memory (leading dimension ld) and
@@ -277,10 +349,11 @@ __device__ inline void load_blocks(double (*d0)[LDP], const double* s0, double (
   put_tile<T1>(d1, v1);
 }
 
-__device__ inline void store_block(double* dst, int ld, const double (*srcb)[LDP]) {
+// The lower triangle of a tile, zeros above it.
+__device__ inline void store_lower(double* dst, int ld, const double (*srcb)[LDP]) {
   for (int e = threadIdx.x; e < B * B; e += blockDim.x) {
     const int i = e >> 6, c = e & 63;
-    dst[(int64_t)i * ld + c] = srcb[i][c];
+    dst[(int64_t)i * ld + c] = (c <= i) ? srcb[i][c] : 0.0;
   }
 }
 
@@ -291,17 +364,14 @@ __global__ __launch_bounds__(kFactorThreads) void k_factor_first(double* __restr
                                                                  int* __restrict__ flag) {
   __shared__ double a[B][LDP];
   __shared__ __align__(16) double x[B][LDP];
-  __shared__ __align__(16) double scr[6 * B];
   double* Ak = A + (int64_t)blockIdx.x * nf * nf;
   double* Wk = W + (int64_t)blockIdx.x * nf * nf;
   if (threadIdx.x < 256) load_block(a, Ak, nf);
   __syncthreads();
-  chol_inv64(a, x, scr, flag);
-  store_block(Ak, nf, a);
-  store_block(Wk, nf, x);
+  chol_inv64(a, x, flag);
+  store_lower(Ak, nf, a);
+  store_lower(Wk, nf, x);
 }
-
-typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 // 64x64x64 product on the fp64 matrix cores (v_mfma_f64_16x16x4f64: A[i][k]
 // from lane i + 16k, B[k][j] from lane j + 16k, D[i][j] in lane
@@ -419,7 +489,6 @@ __global__ __launch_bounds__(kFactorThreads) void k_update(double* __restrict__ 
                                                            int kb, int* __restrict__ flag) {
   __shared__ double p[B][LDP];
   __shared__ __align__(16) double q[B][LDP];
-  __shared__ __align__(16) double scr[6 * B];
   const int k = blockIdx.y;
   const int nbk = nf / B;
   const int T = nbk - kb - 1;
@@ -496,10 +565,10 @@ __global__ __launch_bounds__(kFactorThreads) void k_update(double* __restrict__ 
           for (int v = 0; v < 4; ++v) p[tile_row(a, v)][tile_col(b)] = acc[a][b][v];
     }
     __syncthreads();
-    chol_inv64(p, q, scr, flag);
+    chol_inv64(p, q, flag);
     const int o1 = o + B;
-    store_block(dst, nf, p);
-    store_block(Wk + (int64_t)o1 * nf + o1, nf, q);
+    store_lower(dst, nf, p);
+    store_lower(Wk + (int64_t)o1 * nf + o1, nf, q);
   }
 }
 

@@ -61,3 +61,26 @@ def test_posterior_block_counts(cfg, n):
         np.testing.assert_allclose(g["mu"], o["mu"], rtol=TOL_MU[0], atol=TOL_MU[1])
         np.testing.assert_allclose(g["sigma"], o["sigma"], rtol=TOL_SIGMA[0], atol=TOL_SIGMA[1])
         np.testing.assert_allclose(g["ehvi"], o["ehvi"], rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 47, 48, 64, 65, 127, 129, 200])
+def test_diagonal_block_factor(n):
+    """The 16-column panels of the 64x64 diagonal blocks: every panel and block
+    remainder, against LAPACK in fp64 (inputs and results rounded to fp32 once:
+    2^-24 relative; rows grow by at most the condition number, below 100), and
+    an indefinite pivot in each panel of the first and second block."""
+    import torch
+    import paper_2602_10729_amd as bo
+    _announce("diagonal factor", n)
+    r = np.random.default_rng(n)
+    B = r.standard_normal((n, n))
+    A = (B @ B.T / n + np.eye(n)).astype(np.float32)
+    up = np.triu(np.full((n, n), np.float32(7.0)), 1)            # above: not read
+    L = bo.cholesky_test(torch.from_numpy(np.tril(A) + up).cuda()).cpu().numpy()
+    np.testing.assert_allclose(L, np.linalg.cholesky(A.astype(np.float64)), rtol=2e-7, atol=2e-7)
+    for j in range(0, n, 16):
+        bad = A.copy()
+        bad[j, j] = -1.0
+        with pytest.raises(bo.BoError) as e:
+            bo.cholesky_test(torch.from_numpy(bad).cuda())
+        assert e.value.name == "BO_ERR_NOT_POSITIVE_DEFINITE"
