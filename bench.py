@@ -317,7 +317,7 @@ def main(argv=None):
         "ms_per_step_wall": wall_ms,
         "roofline": {
             "bound": "mfma",
-            "kernel": "k_posterior (one launch per objective)",
+            "kernel": "k_posterior (times per objective; the objectives share one launch)",
             "mfma_dtype": "f16 (three split products per multiply-add, fp32 accumulate)",
             "achieved": achieved,
             "peak": PEAK_FP16_MFMA_TFLOPS,
@@ -387,7 +387,7 @@ def main(argv=None):
         del mc
         c_launch = cpost_ms / max(cl, 1)
         rec["composite_posterior"] = {
-            "bound": "mfma", "kernel": "k_posterior, composite kernel (one launch per objective)",
+            "bound": "mfma", "kernel": "k_posterior, composite kernel (times per objective)",
             "d_route": comp.d_route, "fit_ms": cfit_ms, "launch_ms": c_launch,
             "achieved": flops_launch / (c_launch / 1e3) / 1e12, "peak": PEAK_FP16_MFMA_TFLOPS,
             "unit": "TFLOP/s", "frac": flops_launch / (c_launch / 1e3) / 1e12 / PEAK_FP16_MFMA_TFLOPS,
@@ -409,7 +409,7 @@ def main(argv=None):
     del mf
     f_launch = fpost_ms / max(fl, 1)
     rec["f64_posterior"] = {
-        "bound": "mfma", "kernel": "k_posterior_f64 (one launch per objective)",
+        "bound": "mfma", "kernel": "k_posterior_f64 (times per objective)",
         "launch_ms": f_launch, "achieved": flops_launch / (f_launch / 1e3) / 1e12,
         "peak": PEAK_FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
         "frac": flops_launch / (f_launch / 1e3) / 1e12 / PEAK_FP64_MFMA_TFLOPS,

@@ -475,11 +475,12 @@ bo_status bo_box_decomposition(const float* F, int32_t P, int32_t m,
 
 /*
  * Phase timing for benchmarks. While enabled, every bo_score call records
- * HIP events on its stream before its posterior launches, between them and
+ * HIP events on its stream before its posterior launch, between it and
  * the (q)EHVI launch, and after it. bo_profile_read waits for the recorded
  * events, returns the summed milliseconds of each phase, the number of
- * bo_score calls and the number of posterior launches (one per objective per
- * call) since the last read, and clears them. Enabling resets the counters.
+ * bo_score calls and the number of posteriors (one per objective per call;
+ * the objectives of a call share one launch) since the last read, and clears
+ * them. Enabling resets the counters.
  * Up to 4096 calls are kept; later calls are not timed (see *calls).
  * Errors: INVALID_ARGUMENT (NULL output), DEVICE.
  */

@@ -7,7 +7,7 @@
 //               (bo_score_constrained: the same with feasibility weights);
 //               asynchronous. The box decomposition is rebuilt on the host
 //               only when the reference point changes.
-// bo_argmax   — three tiny launches using the caller's index cell.
+// bo_argmax   — one launch, or three using the caller's index cell.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -609,7 +609,7 @@ size_t score_workspace_floats(const Model& M, int64_t M_, int q, bool have_mu, b
 // objective (into mu_buf, sd_buf and, for q > 1, chol_buf [m][M_][T]), then
 // the EHVI over `boxes` (device, [nbox][2m]). mu_buf and sd_buf are the
 // caller's [npts][m] arrays when mu_user / sd_user, else planar [m][npts]
-// workspace, so that each objective's launch writes whole cache lines.
+// workspace, so that each objective's tiles write whole cache lines.
 // rec (optional) gets profile events.
 bo_status score_launches(const Model& M, const float* cand, int64_t M_, int q,
                          const float* feas_lower, const float* base_samples, int S,
@@ -627,14 +627,17 @@ bo_status score_launches(const Model& M, const float* cand, int64_t M_, int q,
     hipError_t e = hipEventRecord(rec->e[0], st);
     if (e != hipSuccess) return hip_fail(e, "bo_score: profile event");
   }
+  PosteriorBatch pb;
+  pb.m = m;
   for (int k = 0; k < m; ++k) {
-    PosteriorArgs pa = posterior_args(M, k, M.Lp, cand, npts, q);
+    PosteriorArgs& pa = pb.o[k];
+    pa = posterior_args(M, k, M.Lp, cand, npts, q);
     pa.mu = mu_buf + k * mu_ks; pa.mu_ps = mu_ps;
     pa.sd = sd_buf + k * sd_ks; pa.sd_ps = sd_ps;
     pa.chol = chol_buf ? chol_buf + (size_t)k * M_ * T : nullptr;
-    const hipError_t e = M.f64 ? launch_posterior_f64(pa, st) : launch_posterior(pa, st);
-    if ((s = after_launch(e, st, "posterior")) != BO_OK) return s;
   }
+  const hipError_t pe = M.f64 ? launch_posterior_f64(pb, st) : launch_posterior(pb, st);
+  if ((s = after_launch(pe, st, "posterior")) != BO_OK) return s;
   if (rec) {
     hipError_t e = hipEventRecord(rec->e[1], st);
     if (e != hipSuccess) return hip_fail(e, "bo_score: profile event");
@@ -1595,14 +1598,17 @@ bo_status score_nehvi_impl(bo_model model, const float* cand, int64_t M_, int32_
     const int64_t nb_ = std::min<int64_t>(Cb, M_ - b0);
     const int64_t np_ = nb_ * q;
     const float* cc = cand + b0 * q * M.d;
+    PosteriorBatch pb;
+    pb.m = m;
     for (int k = 0; k < m; ++k) {
-      PosteriorArgs pa = posterior_args(M, k, z.Lp0, cc, np_, q);
+      PosteriorArgs& pa = pb.o[k];
+      pa = posterior_args(M, k, z.Lp0, cc, np_, q);
       // chunk-sized planes: the EHVI kernel reads them at the chunk's nbat
       pa.mu = mu_buf + (size_t)k * np_; pa.sd = sd_buf + (size_t)k * np_;
       pa.mu_ps = pa.sd_ps = 1;
       pa.chol = (q > 1) ? ch_buf + (size_t)k * nb_ * T : nullptr;
-      if ((s = after_launch(launch_posterior(pa, st), st, "posterior")) != BO_OK) return s;
     }
+    if ((s = after_launch(launch_posterior(pb, st), st, "posterior")) != BO_OK) return s;
     NehviMeansArgs ma;
     ma.cand = cc; ma.npts = np_; ma.d = M.d; ma.dx = M.dx; ma.n32 = z.n32;
     ma.n_pad = M.n_pad; ma.S = S; ma.Xs = M.Xs; ma.invls = M.invls; ma.Gp = z.Gp;

@@ -376,10 +376,26 @@ struct PosteriorArgs {
   int64_t mu_ps = 1, sd_ps = 1;
   float* chol;         // q > 1: [npts/q][q(q+1)/2] lower factors of this objective, row-major
 };
-hipError_t launch_posterior(const PosteriorArgs& a, hipStream_t st);
+// Up to three objectives of one model in one launch (blockIdx.y: objective):
+// the tiles of a small batch fill the chip together, and a call pays one launch.
+constexpr int kMaxObjectives = 3;
+struct PosteriorBatch {
+  PosteriorArgs o[kMaxObjectives];
+  int m = 0;           // objectives in use; their npts, d, dx, q, nb, dr agree
+  // Objective k's arguments, field by field on the scalar unit: indexed in
+  // memory they would count as divergent, and every buffer load through them
+  // would become a loop over the lanes' descriptors (6.65 -> 8.5 ms a call).
+  __device__ __forceinline__ PosteriorArgs pick(unsigned k) const {
+    PosteriorArgs a = o[0];
+    if (k == 1) a = o[1];
+    if (k == 2) a = o[2];
+    return a;
+  }
+};
+hipError_t launch_posterior(const PosteriorBatch& b, hipStream_t st);
 // The fp64 posterior (posterior_f64.hip): same outputs, from Lp64, alpha64,
 // ils64 and Xraw.
-hipError_t launch_posterior_f64(const PosteriorArgs& a, hipStream_t st);
+hipError_t launch_posterior_f64(const PosteriorBatch& b, hipStream_t st);
 // Blocks per objective of the fp64 fragments (lower 16x32 blocks).
 int64_t posterior_f64_blocks(int nb);
 // Pack W = L^{-1} ([m][nf][nf] fp64) as the fp64 kernel's A fragments.

@@ -3,7 +3,7 @@
 #include "posterior_kernel.h"
 
 namespace bo {
-hipError_t launch_posterior_dx3(const PosteriorArgs& a, hipStream_t st) {
-  return launch_for_dx<3, false>(a, st);
+hipError_t launch_posterior_dx3(const PosteriorBatch& b, hipStream_t st) {
+  return launch_for_dx<3, false>(b, st);
 }
 }  // namespace bo

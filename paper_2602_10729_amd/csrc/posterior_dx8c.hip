@@ -3,7 +3,7 @@
 #include "posterior_kernel.h"
 
 namespace bo {
-hipError_t launch_posterior_comp_dx8(const PosteriorArgs& a, hipStream_t st) {
-  return launch_for_dx<8, true>(a, st);
+hipError_t launch_posterior_comp_dx8(const PosteriorBatch& b, hipStream_t st) {
+  return launch_for_dx<8, true>(b, st);
 }
 }  // namespace bo

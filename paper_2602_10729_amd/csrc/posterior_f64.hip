@@ -77,7 +77,8 @@ __host__ __device__ __forceinline__ int f64_row_start(int I) {
 }
 
 template <int RBW, int NCB, int Q, bool COMP>
-__global__ __launch_bounds__(kThreads) void k_posterior_f64(PosteriorArgs a) {
+__global__ __launch_bounds__(kThreads) void k_posterior_f64(PosteriorBatch batch) {
+  const PosteriorArgs a = batch.pick(blockIdx.y);
   constexpr int NT = 16 * NCB;          // points per tile
   constexpr int PER = kJ * NT / kThreads;   // kernel values per thread per block (1 or 2)
   constexpr int NX = (Q > 1) ? Q : 1;
@@ -350,25 +351,25 @@ __global__ __launch_bounds__(kThreads) void k_posterior_f64(PosteriorArgs a) {
 }
 
 template <int RBW, int NCB, bool COMP>
-hipError_t launch_rb(const PosteriorArgs& a, hipStream_t st) {
+hipError_t launch_rb(const PosteriorBatch& b, hipStream_t st) {
   const int NT = 16 * NCB;
-  const unsigned grid = static_cast<unsigned>((a.npts + NT - 1) / NT);
-  switch (a.q) {
-    case 1: hipLaunchKernelGGL((k_posterior_f64<RBW, NCB, 1, COMP>), dim3(grid), dim3(kThreads), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_posterior_f64<RBW, NCB, 2, COMP>), dim3(grid), dim3(kThreads), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_posterior_f64<RBW, NCB, 4, COMP>), dim3(grid), dim3(kThreads), 0, st, a); break;
+  const unsigned grid = static_cast<unsigned>((b.o[0].npts + NT - 1) / NT);
+  switch (b.o[0].q) {
+    case 1: hipLaunchKernelGGL((k_posterior_f64<RBW, NCB, 1, COMP>), dim3(grid, b.m), dim3(kThreads), 0, st, b); break;
+    case 2: hipLaunchKernelGGL((k_posterior_f64<RBW, NCB, 2, COMP>), dim3(grid, b.m), dim3(kThreads), 0, st, b); break;
+    case 4: hipLaunchKernelGGL((k_posterior_f64<RBW, NCB, 4, COMP>), dim3(grid, b.m), dim3(kThreads), 0, st, b); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <bool COMP>
-hipError_t launch_comp(const PosteriorArgs& a, hipStream_t st) {
+hipError_t launch_comp(const PosteriorBatch& b, hipStream_t st) {
   // every row block of V in the accumulators: 8 waves x RBW slots of 16 rows
-  if (a.nb <= 16) return launch_rb<2, 2, COMP>(a, st);
-  if (a.nb <= 32) return launch_rb<4, 2, COMP>(a, st);
-  if (a.nb <= 64) return launch_rb<8, 2, COMP>(a, st);
-  if (a.nb <= 128) return launch_rb<16, 1, COMP>(a, st);
+  if (b.o[0].nb <= 16) return launch_rb<2, 2, COMP>(b, st);
+  if (b.o[0].nb <= 32) return launch_rb<4, 2, COMP>(b, st);
+  if (b.o[0].nb <= 64) return launch_rb<8, 2, COMP>(b, st);
+  if (b.o[0].nb <= 128) return launch_rb<16, 1, COMP>(b, st);
   return hipErrorInvalidValue;
 }
 
@@ -415,10 +416,11 @@ hipError_t launch_pack_f64(const double* W, int64_t n, int m, int nf, int nb, do
   return hipGetLastError();
 }
 
-hipError_t launch_posterior_f64(const PosteriorArgs& a, hipStream_t st) {
+hipError_t launch_posterior_f64(const PosteriorBatch& b, hipStream_t st) {
+  const PosteriorArgs& a = b.o[0];
   if (a.npts <= 0) return hipSuccess;
   if (a.d > BO_MAX_D) return hipErrorInvalidValue;
-  return a.dr > 0 ? launch_comp<true>(a, st) : launch_comp<false>(a, st);
+  return a.dr > 0 ? launch_comp<true>(b, st) : launch_comp<false>(b, st);
 }
 
 }  // namespace bo

@@ -3,7 +3,8 @@
 // the build compiles them in parallel) and by posterior.hip (shared helpers).
 //
 #pragma once
-// GP posterior of a batch of candidate points, one objective per launch.
+// GP posterior of a batch of candidate points, the objectives of a model side
+// by side in one launch (blockIdx.y).
 //
 // Paper: workflow step (ii) evaluates the acquisition on samples of the
 // joint posterior of the GP surrogates; the posterior of an exact GP at x*
@@ -558,7 +559,8 @@ __device__ __forceinline__ void rounds(const Ctx& C, const PosteriorArgs& a, Pro
 }
 
 template <int NT, int DX4, int Q, int RB, bool COMP>
-__global__ __launch_bounds__(kThreads) void k_posterior(PosteriorArgs a) {
+__global__ __launch_bounds__(kThreads) void k_posterior(PosteriorBatch batch) {
+  const PosteriorArgs a = batch.pick(blockIdx.y);
   extern __shared__ float smem[];
   constexpr int NCB = NT / 16;          // 16-column blocks per tile
   constexpr int NX = (Q > 1) ? Q : 1;   // per-point partial slots (diag + xors)
@@ -952,7 +954,7 @@ static_assert((size_t)kWaves * 64 * 4 <= (size_t)64 * kCSH, "reduction fits the 
 static_assert(2 * 64 * 96 <= 2 * 64 * kCSH, "distance fragments fit the ring");
 
 template <int NT, int DX4, int Q, int RB, bool COMP>
-hipError_t launch_t(const PosteriorArgs& a, hipStream_t st) {
+hipError_t launch_t(const PosteriorBatch& b, hipStream_t st) {
   const size_t lds = sizeof(float) * lds_floats(NT, DX4, Q);
   // more than 64 KiB of dynamic LDS: opt in (cheap; set on every launch so
   // that it holds on whichever device is current)
@@ -960,8 +962,8 @@ hipError_t launch_t(const PosteriorArgs& a, hipStream_t st) {
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      static_cast<int>(lds));
   if (e != hipSuccess) return e;
-  const unsigned grid = static_cast<unsigned>((a.npts + NT - 1) / NT);
-  hipLaunchKernelGGL((k_posterior<NT, DX4, Q, RB, COMP>), dim3(grid), dim3(kThreads), lds, st, a);
+  const unsigned grid = static_cast<unsigned>((b.o[0].npts + NT - 1) / NT);
+  hipLaunchKernelGGL((k_posterior<NT, DX4, Q, RB, COMP>), dim3(grid, b.m), dim3(kThreads), lds, st, b);
   return hipGetLastError();
 }
 
@@ -969,15 +971,15 @@ hipError_t launch_t(const PosteriorArgs& a, hipStream_t st) {
 // 2 row-block slots per wave up to 256 rows, else BO_POST_RB (further rows
 // in passes).
 template <int DX4, bool COMP>
-hipError_t launch_for_dx(const PosteriorArgs& a, hipStream_t st) {
-  const bool small = a.nb <= 16;
-  switch (a.q) {
-    case 1: return small ? launch_t<BO_POST_NT, DX4, 1, 2, COMP>(a, st)
-                         : launch_t<BO_POST_NT, DX4, 1, BO_POST_RB, COMP>(a, st);
-    case 2: return small ? launch_t<BO_POST_NT, DX4, 2, 2, COMP>(a, st)
-                         : launch_t<BO_POST_NT, DX4, 2, BO_POST_RB, COMP>(a, st);
-    case 4: return small ? launch_t<BO_POST_NT, DX4, 4, 2, COMP>(a, st)
-                         : launch_t<BO_POST_NT, DX4, 4, BO_POST_RB, COMP>(a, st);
+hipError_t launch_for_dx(const PosteriorBatch& b, hipStream_t st) {
+  const bool small = b.o[0].nb <= 16;
+  switch (b.o[0].q) {
+    case 1: return small ? launch_t<BO_POST_NT, DX4, 1, 2, COMP>(b, st)
+                         : launch_t<BO_POST_NT, DX4, 1, BO_POST_RB, COMP>(b, st);
+    case 2: return small ? launch_t<BO_POST_NT, DX4, 2, 2, COMP>(b, st)
+                         : launch_t<BO_POST_NT, DX4, 2, BO_POST_RB, COMP>(b, st);
+    case 4: return small ? launch_t<BO_POST_NT, DX4, 4, 2, COMP>(b, st)
+                         : launch_t<BO_POST_NT, DX4, 4, BO_POST_RB, COMP>(b, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -987,20 +989,20 @@ hipError_t launch_for_dx(const PosteriorArgs& a, hipStream_t st) {
 // One per coordinate width and kernel family (posterior_dx<N>.hip: Matern-5/2,
 // posterior_dx<N>c.hip: composite kernel; a composite model needs at least two
 // coordinate groups, so width 4 has no composite instantiation).
-hipError_t launch_posterior_dx1(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_dx2(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_dx3(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_dx4(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_dx5(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_dx6(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_dx7(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_dx8(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_comp_dx2(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_comp_dx3(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_comp_dx4(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_comp_dx5(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_comp_dx6(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_comp_dx7(const PosteriorArgs& a, hipStream_t st);
-hipError_t launch_posterior_comp_dx8(const PosteriorArgs& a, hipStream_t st);
+hipError_t launch_posterior_dx1(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_dx2(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_dx3(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_dx4(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_dx5(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_dx6(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_dx7(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_dx8(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_comp_dx2(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_comp_dx3(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_comp_dx4(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_comp_dx5(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_comp_dx6(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_comp_dx7(const PosteriorBatch& b, hipStream_t st);
+hipError_t launch_posterior_comp_dx8(const PosteriorBatch& b, hipStream_t st);
 
 }  // namespace bo

@@ -164,3 +164,24 @@ def test_noisy_three_objective_draw_groups(q, S):
     Zs = wl.Z[:, 0, :] if q == 1 else wl.Z
     o = O.nehvi(oracle_fit(wl), wl.cand.astype(np.float64), wl.ref.astype(np.float64), ZX, Zs)
     np.testing.assert_allclose(e, o["ehvi"], rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
+
+
+@pytest.mark.parametrize("M", [0, 1, 63, 1023, 1025, 16383, 16384, 16385])
+def test_argmax_one_launch_line(M):
+    """Either side of the one-workgroup argmax: ties take the lowest index, NaN
+    never wins, nothing to choose gives -1."""
+    import torch
+    import paper_2602_10729_amd as bo
+    _announce("argmax line", M)
+    r = np.random.default_rng(M)
+    v = r.standard_normal(M).astype(np.float32)
+    for values in (v, np.full(M, np.nan, np.float32), np.full(M, -np.inf, np.float32)):
+        if M > 64 and values is v:
+            values[[M - 1, M // 2, 7]] = 9.0
+            values[3] = np.nan
+        i, x = bo.argmax(to_dev(values))
+        ok = ~np.isnan(values)
+        if not ok.any():
+            assert int(i) == -1 and np.isnan(float(x))
+        else:
+            assert int(i) == int(np.nanargmax(values)) and float(x) == np.nanmax(values)
