@@ -252,8 +252,9 @@ __device__ __forceinline__ void block16(double* dst, const double* P, const doub
 // A barrier ends each part. Bound by the serial chain of the 64 pivots, about
 // 175 cycles each in one wave's registers; eight waves with a barrier and an
 // LDS round trip per pivot took 650. 64x64 block in LDS: 41.5e3 -> 21.5e3
-// cycles; k_factor_first (one block) 21.5 -> 11.7 us, k_update at n = 1024,
-// m = 2 25.2 -> 16.6 us, at n = 2048, m = 3 38.4 -> 30.0 us.
+// cycles; k_factor_first (one block) 21.5 -> 11.7 us, k_update with it at
+// n = 1024, m = 2 25.2 -> 16.6 us, at n = 2048, m = 3 38.4 -> 30.0 us (its tile
+// products then in four waves, see gemm_nt_64).
 constexpr int kFactorThreads = 512;
 __device__ __forceinline__ void chol_inv64(double (*a)[LDP], double (*x)[LDP], int* flag) {
   const int l = threadIdx.x & 63;
@@ -311,42 +312,44 @@ __device__ __forceinline__ void chol_inv64(double (*a)[LDP], double (*x)[LDP], i
 }
 
 // Copies of 64x64 tiles between global memory (leading dimension ld) and
-// padded LDS tiles, by the first 256 threads of a workgroup. Every load of a call is
-// issued before the first LDS store, so the latencies overlap; two tiles
-// can be fetched in one call. Transposed variants store dst[c][i] = src[i][c].
-template <bool T>
-__device__ __forceinline__ void put_tile(double (*dst)[LDP], const double (&v)[16]) {
+// padded LDS tiles, by the NTH threads of a workgroup (or its first NTH). Every
+// load of a call is issued before the first LDS store, so the latencies
+// overlap; two tiles can be fetched in one call. Transposed variants store
+// dst[c][i] = src[i][c].
+template <bool T, int NTH>
+__device__ __forceinline__ void put_tile(double (*dst)[LDP], const double (&v)[B * B / NTH]) {
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int e = threadIdx.x + 256 * k, i = e >> 6, c = e & 63;
+  for (int k = 0; k < B * B / NTH; ++k) {
+    const int e = threadIdx.x + NTH * k, i = e >> 6, c = e & 63;
     if (T) dst[c][i] = v[k];
     else dst[i][c] = v[k];
   }
 }
 
-__device__ __forceinline__ void get_tile(double (&v)[16], const double* src, int ld) {
+template <int NTH>
+__device__ __forceinline__ void get_tile(double (&v)[B * B / NTH], const double* src, int ld) {
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int e = threadIdx.x + 256 * k, i = e >> 6, c = e & 63;
+  for (int k = 0; k < B * B / NTH; ++k) {
+    const int e = threadIdx.x + NTH * k, i = e >> 6, c = e & 63;
     v[k] = src[(int64_t)i * ld + c];
   }
 }
 
-template <bool T0 = false>
+template <int NTH>
 __device__ inline void load_block(double (*dst)[LDP], const double* src, int ld) {
-  double v[16];
-  get_tile(v, src, ld);
-  put_tile<T0>(dst, v);
+  double v[B * B / NTH];
+  get_tile<NTH>(v, src, ld);
+  put_tile<false, NTH>(dst, v);
 }
 
-template <bool T0, bool T1>
-__device__ inline void load_blocks(double (*d0)[LDP], const double* s0, double (*d1)[LDP],
-                                   const double* s1, int ld) {
-  double v0[16], v1[16];
-  get_tile(v0, s0, ld);
-  get_tile(v1, s1, ld);
-  put_tile<T0>(d0, v0);
-  put_tile<T1>(d1, v1);
+template <bool T0, bool T1, int NTH>
+__device__ inline void load_blocks(double (*d0)[LDP], const double* s0, int ld0, double (*d1)[LDP],
+                                   const double* s1, int ld1) {
+  double v0[B * B / NTH], v1[B * B / NTH];
+  get_tile<NTH>(v0, s0, ld0);
+  get_tile<NTH>(v1, s1, ld1);
+  put_tile<T0, NTH>(d0, v0);
+  put_tile<T1, NTH>(d1, v1);
 }
 
 // The lower triangle of a tile, zeros above it.
@@ -358,7 +361,6 @@ __device__ inline void store_lower(double* dst, int ld, const double (*srcb)[LDP
 }
 
 // First diagonal block (kb = 0) of every objective: L into A, L^{-1} into W.
-// Eight waves (the factor's layout); the first four load the tile.
 __global__ __launch_bounds__(kFactorThreads) void k_factor_first(double* __restrict__ A,
                                                                  double* __restrict__ W, int nf,
                                                                  int* __restrict__ flag) {
@@ -366,7 +368,7 @@ __global__ __launch_bounds__(kFactorThreads) void k_factor_first(double* __restr
   __shared__ __align__(16) double x[B][LDP];
   double* Ak = A + (int64_t)blockIdx.x * nf * nf;
   double* Wk = W + (int64_t)blockIdx.x * nf * nf;
-  if (threadIdx.x < 256) load_block(a, Ak, nf);
+  load_block<kFactorThreads>(a, Ak, nf);
   __syncthreads();
   chol_inv64(a, x, flag);
   store_lower(Ak, nf, a);
@@ -375,28 +377,29 @@ __global__ __launch_bounds__(kFactorThreads) void k_factor_first(double* __restr
 
 // 64x64x64 product on the fp64 matrix cores (v_mfma_f64_16x16x4f64: A[i][k]
 // from lane i + 16k, B[k][j] from lane j + 16k, D[i][j] in lane
-// j + 16(i%4), element i/4): wave w (of the first four) adds
-// sum_t P[i][t] Q[c][t] over its 32x32 quadrant, rows 32(w/2).., columns
-// 32(w%2).., as 2x2 tiles of 16x16;
-// acc[a][b][v] is element (32(w/2) + 16a + lane/16 + 4v,
-// 32(w%2) + 16b + lane%16) (tile_row / tile_col below).
+// j + 16(i%4), element i/4): wave w of eight adds sum_t P[i][t] Q[c][t] over
+// rows 16(w/2).. and columns 32(w%2).., two tiles of 16x16; acc[b][v] is element
+// (16(w/2) + lane/16 + 4v, 32(w%2) + 16b + lane%16) (tile_row / tile_col below).
+// Two waves a SIMD, so that one's operand reads hide behind the other's
+// products, and twice the loads in flight: against four waves of 2x2 tiles
+// k_update at n = 1024, m = 2 16.6 -> 15.7 us, at n = 2048, m = 3 30.0 -> 28.2
+// us, K^{-1} (sixteen products in a row) at n = 1024 56.4 -> 52.8 us.
+constexpr int kTileThreads = 512;
 __device__ __forceinline__ void gemm_nt_64(const double (*P)[LDP], const double (*Q)[LDP],
-                                           doublex4 (&acc)[2][2]) {
+                                           doublex4 (&acc)[2]) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int r0 = 32 * (w >> 1) + (l & 15), c0 = 32 * (w & 1) + (l & 15), kq = l >> 4;
-#pragma unroll 4
+  const int r0 = 16 * (w >> 1) + (l & 15), c0 = 32 * (w & 1) + (l & 15), kq = l >> 4;
+#pragma unroll
   for (int t = 0; t < B; t += 4) {
-    const double a0 = P[r0][t + kq], a1 = P[r0 + 16][t + kq];
+    const double a0 = P[r0][t + kq];
     const double b0 = Q[c0][t + kq], b1 = Q[c0 + 16][t + kq];
-    acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-    acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-    acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+    acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0], 0, 0, 0);
+    acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[1], 0, 0, 0);
   }
 }
-__device__ __forceinline__ int tile_row(int a, int v) {
+__device__ __forceinline__ int tile_row(int v) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  return 32 * (w >> 1) + 16 * a + (l >> 4) + 4 * v;
+  return 16 * (w >> 1) + (l >> 4) + 4 * v;
 }
 __device__ __forceinline__ int tile_col(int b) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -433,13 +436,13 @@ __global__ __launch_bounds__(256) void k_panel(double* __restrict__ A, double* _
       const int g = tid + 256 * e;
       v0[e] = dst[(int64_t)(g >> 6) * nf + (g & 63)];
     }
-    get_tile(v1, D, nf);
+    get_tile<256>(v1, D, nf);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int g = tid + 256 * e;
       p[g >> 6][g & 63] = v0[e];
     }
-    put_tile<false>(q, v1);
+    put_tile<false, 256>(q, v1);
     __syncthreads();
     // wave w: output columns 16w .. 16w+15 (one 16x16 tile on the matrix cores)
     doublex4 acc = {};
@@ -454,13 +457,13 @@ __global__ __launch_bounds__(256) void k_panel(double* __restrict__ A, double* _
   } else {
     double* dst = Wk + (int64_t)o * nf + (t - T) * B + 16 * u;
     // p = D; q[c][s] = R[s][16u + c] (c < 16)
-    get_tile(v1, D, nf);
+    get_tile<256>(v1, D, nf);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int g = tid + 256 * e;
       v0[e] = dst[(int64_t)(g >> 4) * nf + (g & 15)];
     }
-    put_tile<false>(p, v1);
+    put_tile<false, 256>(p, v1);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int g = tid + 256 * e;
@@ -497,9 +500,6 @@ __global__ __launch_bounds__(kFactorThreads) void k_update(double* __restrict__ 
   double* Ak = A + (int64_t)k * nf * nf;
   double* Wk = W + (int64_t)k * nf * nf;
   const int o = kb * B;
-  // eight waves (the diagonal factor's layout): the first four load and
-  // multiply the tile, all eight factor the next diagonal block
-  const bool prod = threadIdx.x < 256;
   double* dst;
   bool first_r = false;
   if (t < nsyrk) {
@@ -509,9 +509,8 @@ __global__ __launch_bounds__(kFactorThreads) void k_update(double* __restrict__ 
     while (r * (r + 1) / 2 > t) --r;
     const int ib = kb + 1 + r;
     const int cb = kb + 1 + (t - r * (r + 1) / 2);
-    if (prod)
-      load_blocks<false, false>(p, Ak + (int64_t)ib * B * nf + o,      // L[ib][kb]
-                                q, Ak + (int64_t)cb * B * nf + o, nf); // L[cb][kb]
+    load_blocks<false, false, kTileThreads>(p, Ak + (int64_t)ib * B * nf + o, nf,    // L[ib][kb]
+                                            q, Ak + (int64_t)cb * B * nf + o, nf);   // L[cb][kb]
     dst = Ak + (int64_t)ib * B * nf + cb * B;
   } else {
     // R tile (ib, jb): ib > kb, jb <= kb:  W[ib][jb] -= L[ib][kb] W[kb][jb]
@@ -519,51 +518,37 @@ __global__ __launch_bounds__(kFactorThreads) void k_update(double* __restrict__ 
     const int ib = kb + 1 + u / (kb + 1);
     const int jb = u % (kb + 1);
     first_r = (jb == kb);
-    if (prod)
-      load_blocks<false, true>(p, Ak + (int64_t)ib * B * nf + o,        // L[ib][kb]
-                               q, Wk + (int64_t)o * nf + jb * B, nf);   // q = W[kb][jb]^T
+    load_blocks<false, true, kTileThreads>(p, Ak + (int64_t)ib * B * nf + o, nf,     // L[ib][kb]
+                                           q, Wk + (int64_t)o * nf + jb * B, nf);    // q = W[kb][jb]^T
     dst = Wk + (int64_t)ib * B * nf + jb * B;
   }
   // the tile's current values, requested before the product: the first
   // update of an R tile (jb = kb) starts from zero instead (W is not cleared
   // beforehand; its blocks above the diagonal are never read)
-  doublex4 cur[2][2] = {};
-  if (prod) {
+  doublex4 cur[2] = {};
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+  for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          cur[a][b][v] = first_r ? 0.0 : dst[(int64_t)tile_row(a, v) * nf + tile_col(b)];
-  }
+    for (int v = 0; v < 4; ++v)
+      cur[b][v] = first_r ? 0.0 : dst[(int64_t)tile_row(v) * nf + tile_col(b)];
   __syncthreads();
-  doublex4 acc[2][2] = {};
-  if (prod) {
-    gemm_nt_64(p, q, acc);
+  doublex4 acc[2] = {};
+  gemm_nt_64(p, q, acc);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+  for (int b = 0; b < 2; ++b) {
+    acc[b] = cur[b] - acc[b];
+    // the next diagonal tile (t = 0) is stored once, factored, below
+    if (t != 0)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        acc[a][b] = cur[a][b] - acc[a][b];
-        // the next diagonal tile (t = 0) is stored once, factored, below
-        if (t != 0)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            dst[(int64_t)tile_row(a, v) * nf + tile_col(b)] = acc[a][b][v];
-      }
+      for (int v = 0; v < 4; ++v) dst[(int64_t)tile_row(v) * nf + tile_col(b)] = acc[b][v];
   }
   if (t == 0) {
     // next diagonal block: stage the updated tile, factor and invert it
     __syncthreads();
-    if (prod) {
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) p[tile_row(a, v)][tile_col(b)] = acc[a][b][v];
-    }
+      for (int v = 0; v < 4; ++v) p[tile_row(v)][tile_col(b)] = acc[b][v];
     __syncthreads();
     chol_inv64(p, q, flag);
     const int o1 = o + B;
@@ -943,7 +928,7 @@ __global__ __launch_bounds__(256) void k_logdet_quad(const double* __restrict__ 
 
 // K^{-1} = W^T W into the lower 64-blocks of A: tile (I, J), I >= J, sums
 // W[K][I]^T W[K][J] over K >= I (W is zero above its diagonal).
-__global__ __launch_bounds__(256) void k_kinv(double* __restrict__ A, const double* __restrict__ W,
+__global__ __launch_bounds__(kTileThreads) void k_kinv(double* __restrict__ A, const double* __restrict__ W,
                                               int nf) {
   __shared__ double p[B][LDP];
   __shared__ double q[B][LDP];
@@ -955,21 +940,19 @@ __global__ __launch_bounds__(256) void k_kinv(double* __restrict__ A, const doub
   const int J = t - I * (I + 1) / 2;
   const int nbk = nf / B;
   const double* Wk = W + (int64_t)k * nf * nf;
-  doublex4 acc[2][2] = {};
+  doublex4 acc[2] = {};
   for (int K = I; K < nbk; ++K) {
     __syncthreads();   // the previous step's tiles are no longer read
-    load_blocks<true, true>(p, Wk + (int64_t)K * B * nf + I * B,
-                            q, Wk + (int64_t)K * B * nf + J * B, nf);
+    load_blocks<true, true, kTileThreads>(p, Wk + (int64_t)K * B * nf + I * B, nf,
+                                          q, Wk + (int64_t)K * B * nf + J * B, nf);
     __syncthreads();
     gemm_nt_64(p, q, acc);
   }
   double* dst = A + (int64_t)k * nf * nf + (int64_t)I * B * nf + J * B;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) dst[(int64_t)tile_row(a, v) * nf + tile_col(b)] = acc[a][b][v];
+    for (int v = 0; v < 4; ++v) dst[(int64_t)tile_row(v) * nf + tile_col(b)] = acc[b][v];
 }
 
 // Gradient partials of one 16x16 tile of observation pairs (i >= i') per
@@ -1118,7 +1101,7 @@ __global__ __launch_bounds__(256) void k_gather_z(const float* __restrict__ ZX, 
 // identity or transpose; Bm, C [nf][ldb]. One 64x64 tile of C per workgroup,
 // over the 64-blocks of T that the triangle leaves non-zero.
 template <bool TRANS>
-__global__ __launch_bounds__(256) void k_trmm(const double* __restrict__ T,
+__global__ __launch_bounds__(kTileThreads) void k_trmm(const double* __restrict__ T,
                                               const double* __restrict__ Bm,
                                               double* __restrict__ C, int nf, int ldb) {
   __shared__ double p[B][LDP];
@@ -1127,26 +1110,22 @@ __global__ __launch_bounds__(256) void k_trmm(const double* __restrict__ T,
   const int nbk = nf / B;
   const double* Tk = T + (int64_t)k * nf * nf;
   const double* Bk = Bm + (int64_t)k * nf * ldb;
-  doublex4 acc[2][2] = {};
+  doublex4 acc[2] = {};
   const int k0 = TRANS ? I : 0, k1 = TRANS ? nbk : I + 1;
   for (int K = k0; K < k1; ++K) {
     __syncthreads();   // the previous step's tiles are no longer read
-    double v0[16], v1[16];
     // P[i][t] = op(T)[I*B + i][K*B + t]; Q[c][t] = Bm[K*B + t][Jc*B + c]
-    get_tile(v0, TRANS ? Tk + (int64_t)K * B * nf + I * B : Tk + (int64_t)I * B * nf + K * B, nf);
-    get_tile(v1, Bk + (int64_t)K * B * ldb + Jc * B, ldb);
-    put_tile<TRANS>(p, v0);
-    put_tile<true>(q, v1);
+    load_blocks<TRANS, true, kTileThreads>(
+        p, TRANS ? Tk + (int64_t)K * B * nf + I * B : Tk + (int64_t)I * B * nf + K * B, nf,
+        q, Bk + (int64_t)K * B * ldb + Jc * B, ldb);
     __syncthreads();
     gemm_nt_64(p, q, acc);
   }
   double* dst = C + (int64_t)k * nf * ldb + (int64_t)I * B * ldb + Jc * B;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) dst[(int64_t)tile_row(a, v) * ldb + tile_col(b)] = acc[a][b][v];
+    for (int v = 0; v < 4; ++v) dst[(int64_t)tile_row(v) * ldb + tile_col(b)] = acc[b][v];
 }
 
 }  // namespace
@@ -1209,7 +1188,7 @@ hipError_t launch_mll(const float* X, int64_t n, int d, int m, int nf, const Gra
                       double* partials, double* out, hipStream_t st) {
   hipLaunchKernelGGL(k_logdet_quad, dim3(m), dim3(256), 0, st, A, tmp, n, nf, out, d);
   const int nbk = nf / B;
-  hipLaunchKernelGGL(k_kinv, dim3(nbk * (nbk + 1) / 2, m), dim3(256), 0, st, A, W, nf);
+  hipLaunchKernelGGL(k_kinv, dim3(nbk * (nbk + 1) / 2, m), dim3(kTileThreads), 0, st, A, W, nf);
   const int64_t tiles = mll_tiles(nf);
   hipLaunchKernelGGL(k_mll_grad, dim3(static_cast<unsigned>(tiles), m), dim3(256), 0, st, X, n,
                      d, nf, g, A, alpha64, partials);
@@ -1243,7 +1222,7 @@ hipError_t launch_pack_x(const float* Xs, int64_t n, int m, int nb, int dx, int 
 
 hipError_t launch_kinv(double* A, const double* W, int nf, int m, hipStream_t st) {
   const int nbk = nf / B;
-  hipLaunchKernelGGL(k_kinv, dim3(nbk * (nbk + 1) / 2, m), dim3(256), 0, st, A, W, nf);
+  hipLaunchKernelGGL(k_kinv, dim3(nbk * (nbk + 1) / 2, m), dim3(kTileThreads), 0, st, A, W, nf);
   return hipGetLastError();
 }
 
@@ -1265,8 +1244,8 @@ hipError_t launch_trmm(bool trans, const double* T, const double* Bm, double* C,
                        int ldb, int m, hipStream_t st) {
   if (nf % B != 0 || ldb % B != 0) return hipErrorInvalidValue;
   const dim3 grid(ldb / B, nf / B, m);
-  if (trans) hipLaunchKernelGGL(k_trmm<true>, grid, dim3(256), 0, st, T, Bm, C, nf, ldb);
-  else hipLaunchKernelGGL(k_trmm<false>, grid, dim3(256), 0, st, T, Bm, C, nf, ldb);
+  if (trans) hipLaunchKernelGGL(k_trmm<true>, grid, dim3(kTileThreads), 0, st, T, Bm, C, nf, ldb);
+  else hipLaunchKernelGGL(k_trmm<false>, grid, dim3(kTileThreads), 0, st, T, Bm, C, nf, ldb);
   return hipGetLastError();
 }
 
