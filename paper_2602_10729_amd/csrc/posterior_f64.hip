@@ -1,5 +1,5 @@
 // GP posterior of a batch of candidate points in fp64 (models fitted with
-// bo_fit_f64 / bo_fit_composite_f64), one objective per launch.
+// bo_fit_f64 / bo_fit_composite_f64), the objectives side by side in one launch.
 //
 // Paper: implementation section (the GP kernels run in double precision);
 // the posterior of an exact GP at x* is mu = k*^T alpha and
@@ -222,11 +222,11 @@ __global__ __launch_bounds__(kThreads) void k_posterior_f64(PosteriorBatch batch
       const int I = slotI[t];
       if (I < nb && 2 * J <= I) {
         // A fragment of block (I, J): W[16 I + lane % 16][32 J + 4 kk + lane / 16]
-        const double* ap = a.Lp64 + ((int64_t)(f64_row_start(I) + J) * 64 + lane) * 8;
+        const double* ap = a.Lp64 + (int64_t)(f64_row_start(I) + J) * 512 + lane * 2;
         double afr[8];
 #pragma unroll
         for (int kk = 0; kk < 8; kk += 2) {
-          const double2 v = *reinterpret_cast<const double2*>(ap + kk);
+          const double2 v = *reinterpret_cast<const double2*>(ap + 64 * kk);
           afr[kk] = v.x;
           afr[kk + 1] = v.y;
         }
@@ -376,7 +376,12 @@ hipError_t launch_comp(const PosteriorBatch& b, hipStream_t st) {
 // Pack W = L^{-1} (fp64, [m][nf][nf], lower) as A fragments of
 // v_mfma_f64_16x16x4f64: block (I, J) of 16 rows x 32 columns at index
 // f64_row_start(I) + J, lane l holding W[16 I + l%16][32 J + 4 kk + l/16] for
-// kk = 0..7 (zero above the diagonal and past n), 4 KiB per block.
+// kk = 0..7 (zero above the diagonal and past n), 4 KiB per block: pairs of kk,
+// each pair 16 bytes of every lane in lane order, so that a load instruction
+// reads 1 KiB in a row (a lane's eight values together made it touch every line
+// of the block, four times over: 65536 points, n = 1024 1.66 -> 1.63 ms per
+// objective). Requesting the next slot's fragment before a slot's products is
+// slower with either layout (1.78 ms with this one).
 __global__ __launch_bounds__(256) void k_pack_f64(const double* __restrict__ W, int64_t n, int nf,
                                                   int64_t nblk, double* __restrict__ Lp) {
   const int k = blockIdx.y;
@@ -397,10 +402,10 @@ __global__ __launch_bounds__(256) void k_pack_f64(const double* __restrict__ W, 
   }
   const int64_t row = (int64_t)I * 16 + lane % 16;
   const double* Wk = W + (int64_t)k * nf * nf;
-  double* dst = Lp + ((int64_t)k * nblk + blk) * 512 + lane * 8;
+  double* dst = Lp + ((int64_t)k * nblk + blk) * 512 + lane * 2;
   for (int kk = 0; kk < 8; ++kk) {
     const int64_t col = (int64_t)J * 32 + 4 * kk + lane / 16;
-    dst[kk] = (row < n && col <= row) ? Wk[row * nf + col] : 0.0;
+    dst[64 * (kk & ~1) + (kk & 1)] = (row < n && col <= row) ? Wk[row * nf + col] : 0.0;
   }
 }
 
