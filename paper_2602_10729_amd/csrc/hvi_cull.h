@@ -9,9 +9,11 @@
 // member's largest value per objective over the wave is reduced with DPP, lane
 // i compares box c0 + i's lower corner with it, and the ballots are one 64-bit
 // mask of the boxes that the member may reach. The waves then visit only those
-// boxes, by which members reach them: one (its own extent product), two (two
-// products less their intersection), more (all 2^Q - 1 subsets). Every term
-// left out is exactly zero on every lane. A box's corner and widths come
+// boxes, in order, by which members reach them: one (its own extent product),
+// two (two products less their intersection), more (all 2^Q - 1 subsets).
+// Every term left out is exactly zero on every lane, and a lane adds the others
+// box after box whatever the way taken: which boxes and ways these are depends
+// on the batches that share the wave, a batch's sum does not. A box's corner and widths come
 // through the scalar cache (its address is uniform) as scalar operands; the
 // visits are bound by scalar issue (mask and address), so one box at a time or
 // four measured 2-13% slower than two, and at q = 1, where the terms are
@@ -71,85 +73,83 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
       two |= any & m[a];
       any |= m[a];
     }
-    auto extents = [&](const float (&v)[3], unsigned c, float (&e)[3]) {
+    struct Box { float lo[3], w[3]; };
+    auto box = [&](unsigned c) {
       const const_floats p = bx + 6u * c;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) e[k] = __builtin_amdgcn_fmed3f(v[k] - p[k], 0.0f, p[3 + k]);
+      return Box{{p[0], p[1], p[2]}, {p[3], p[4], p[5]}};
     };
-    // boxes that only member a reaches: two at a time, so that one's corner is
-    // on its way while the other is used
+    auto extents = [&](const float (&v)[3], const Box& b, float (&e)[3]) {
 #pragma unroll
-    for (int a = 0; a < Q; ++a) {
-      uint64_t r = m[a] & ~two;
-      if (Q == 1 && __builtin_popcountll(r) > 48) {
-        // the wave's lanes are far apart: all of the chunk in order
-        const unsigned c1 = min(c0 + 64, nbox);
+      for (int k = 0; k < 3; ++k) e[k] = __builtin_amdgcn_fmed3f(v[k] - b.lo[k], 0.0f, b.w[k]);
+    };
+    auto own = [&](const float (&v)[3], const Box& b) {
+      float e[3];
+      extents(v, b, e);
+      pos = fmaf(e[0] * e[1], e[2], pos);
+    };
+    if (Q == 1 && __builtin_popcountll(any) > 48) {
+      // the wave's lanes are far apart: all of the chunk in order
+      const unsigned c1 = min(c0 + 64, nbox);
 #pragma unroll 4
-        for (unsigned c = c0; c < c1; ++c) {
-          float e[3];
-          extents(y[a], c, e);
-          pos = fmaf(e[0] * e[1], e[2], pos);
-        }
-        continue;
-      }
-      while (r) {
-        unsigned c[2];
-        bool on[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          on[i] = r != 0;
-          c[i] = r ? c0 + __builtin_ctzll(r) : c[0];
-          r &= r - 1;
-        }
-        float e[2][3];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) extents(y[a], c[i], e[i]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-          if (on[i]) pos = fmaf(e[i][0] * e[i][1], e[i][2], pos);
-      }
+      for (unsigned c = c0; c < c1; ++c) own(y[0], box(c));
+      continue;
     }
-    if constexpr (Q > 1) {
-      if (two & ~more) {
+    // box i of the chunk, by the members that reach it
+    auto visit = [&](unsigned i, const Box& b) {
+      const uint64_t bit = 1ull << i;
+      if (Q == 1) {
+        own(y[0], b);
+      } else if (!(two & bit)) {
+        if (Q == 4 && ((m[Q - 1] | m[Q - 2]) & bit)) {
+          if (m[Q - 1] & bit) own(y[Q - 1], b);
+          else own(y[Q - 2], b);
+        } else {
+          if (m[1] & bit) own(y[1], b);
+          else own(y[0], b);
+        }
+      } else if (Q == 2 || !(more & bit)) {
 #pragma unroll
         for (int a = 0; a < Q; ++a)
 #pragma unroll
-          for (int b = a + 1; b < Q; ++b) {
-            uint64_t r = m[a] & m[b] & ~more;
-            while (r) {
-              const unsigned c = c0 + __builtin_ctzll(r);
-              r &= r - 1;
+          for (int d = a + 1; d < Q; ++d)
+            if (Q == 2 || (m[a] & m[d] & bit)) {
               float e[3], f[3];
-              extents(y[a], c, e);
-              extents(y[b], c, f);
+              extents(y[a], b, e);
+              extents(y[d], b, f);
               pos = fmaf(e[0] * e[1], e[2], pos);
               pos = fmaf(f[0] * f[1], f[2], pos);
               neg = fmaf(fminf(e[0], f[0]) * fminf(e[1], f[1]), fminf(e[2], f[2]), neg);
             }
+      } else {
+        constexpr int NS = 1 << Q;
+        float ext[NS][3];
+#pragma unroll
+        for (int a = 0; a < Q; ++a) extents(y[a], b, ext[1 << a]);
+#pragma unroll
+        for (int mask = 1; mask < NS; ++mask) {
+          const int low = mask & (-mask);
+          if (mask != low) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ext[mask][k] = fminf(ext[mask ^ low][k], ext[low][k]);
           }
-      }
-      if constexpr (Q > 2) {
-        uint64_t r = more;
-        while (r) {
-          const unsigned c = c0 + __builtin_ctzll(r);
-          r &= r - 1;
-          constexpr int NS = 1 << Q;
-          float ext[NS][3];
-#pragma unroll
-          for (int a = 0; a < Q; ++a) extents(y[a], c, ext[1 << a]);
-#pragma unroll
-          for (int mask = 1; mask < NS; ++mask) {
-            const int low = mask & (-mask);
-            if (mask != low) {
-#pragma unroll
-              for (int k = 0; k < 3; ++k) ext[mask][k] = fminf(ext[mask ^ low][k], ext[low][k]);
-            }
-            const float t = ext[mask][0] * ext[mask][1];
-            if (__builtin_popcount(mask) & 1) pos = fmaf(t, ext[mask][2], pos);
-            else neg = fmaf(t, ext[mask][2], neg);
-          }
+          const float t = ext[mask][0] * ext[mask][1];
+          if (__builtin_popcount(mask) & 1) pos = fmaf(t, ext[mask][2], pos);
+          else neg = fmaf(t, ext[mask][2], neg);
         }
       }
+    };
+    // two boxes at a time, so that one's corner is on its way while the other
+    // is used
+    uint64_t r = any;
+    while (r) {
+      const unsigned i0 = __builtin_ctzll(r);
+      r &= r - 1;
+      const bool second = r != 0;
+      const unsigned i1 = second ? __builtin_ctzll(r) : i0;
+      r &= r - 1;
+      const Box b0 = box(c0 + i0), b1 = box(c0 + i1);
+      visit(i0, b0);
+      if (second) visit(i1, b1);
     }
   }
 }
