@@ -58,6 +58,15 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
   for (int a = 0; a < Q; ++a)
 #pragma unroll
     for (int k = 0; k < 3; ++k) top[a][k] = wave_max(y[a][k]);
+  // An infinite value times an extent of zero is NaN, so a box that a lane does
+  // not reach counts as well then: all boxes are marked, whatever the lanes
+  // beside it hold. (Bits of floats: +inf is above every number.)
+  int largest = __float_as_int(top[0][0]);
+#pragma unroll
+  for (int a = 0; a < Q; ++a)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) largest = max(largest, __float_as_int(top[a][k]));
+  const uint64_t inf = largest >= 0x7f800000 ? ~0ull : 0ull;
   const const_floats bx = (const_floats)(uintptr_t)boxes;
   const int lane = threadIdx.x & 63;
   for (int c0 = 0; c0 < nbox; c0 += 64) {
@@ -69,6 +78,7 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
     for (int a = 0; a < Q; ++a) {
       m[a] = __builtin_amdgcn_ballot_w64(l[0] < top[a][0]) & __builtin_amdgcn_ballot_w64(l[1] < top[a][1]) &
              __builtin_amdgcn_ballot_w64(l[2] < top[a][2]);
+      m[a] |= inf & (nbox - c0 < 64 ? (1ull << (nbox - c0)) - 1 : ~0ull);
       more |= two & m[a];
       two |= any & m[a];
       any |= m[a];

@@ -163,6 +163,35 @@ def test_three_objective_batch_order(P, q, ls):
         np.testing.assert_array_equal(g, got[0][o])
 
 
+@pytest.mark.parametrize("q", [1, 2, 4])
+def test_three_objective_infinite_samples(q):
+    """An infinite sample of one objective: its product with a box that the
+    batch does not reach is 0 * inf, so the value is NaN as it is box by box,
+    with any batches beside it and alone; the same for the noisy acquisition."""
+    import torch
+    import paper_2602_10729_amd as bo
+    _announce("infinite samples", q)
+    wl = _front_workload(12, q, 20, 100, seed=6)
+    wl.Z[7, 0, 1] = np.inf
+    full = gpu_run(wl)
+    model, cand, Z = full["model"], to_dev(wl.cand), to_dev(wl.Z)
+    one = [float(bo.score(model, cand[i:i + 1].contiguous(), wl.ref, Z)) for i in range(100)]
+    np.testing.assert_array_equal(full["ehvi"], np.float32(one))
+    if q == 1:
+        lo, hi = bo.box_decomposition(wl.Y[full["front"]], wl.ref)
+        y = full["mu"][:, 0] + full["sigma"][:, 0] * wl.Z[7, 0]              # [100, 3]
+        with np.errstate(invalid="ignore"):
+            ext = np.minimum(np.maximum(y[:, None] - lo, 0.0), hi - lo)
+            want = ext.prod(axis=2).sum(axis=1)
+        assert np.isnan(want).any()
+        np.testing.assert_array_equal(np.isnan(full["ehvi"]), np.isnan(want))
+    ZX = np.random.default_rng(9).standard_normal((20, 12, 3)).astype(np.float32)
+    bo.nehvi_prepare(model, to_dev(ZX), wl.ref)
+    e = bo.score_nehvi(model, cand, Z).cpu().numpy()
+    one = [float(bo.score_nehvi(model, cand[i:i + 1].contiguous(), Z)) for i in range(100)]
+    np.testing.assert_array_equal(e, np.float32(one))
+
+
 def test_three_objective_samples_at_the_lds_limit():
     """The largest S of q = 4 with three objectives: the samples leave no room
     in LDS for the boxes' corners, which then come from global memory."""
