@@ -360,6 +360,7 @@ __global__ __launch_bounds__(1024) void k_ehvi3(EhviArgs a, bool lds_lo) {
     }
   const int gs = (a.S + kGroups - 1) / kGroups;      // samples per group
   float sum[kGroups / 4];                            // this wave's groups (W >= 4)
+  int walk = 0;
 #pragma unroll
   for (int gi = 0; gi < kGroups / 4; ++gi) {
     const int g = wave * (kGroups / W) + gi;
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(1024) void k_ehvi3(EhviArgs a, bool lds_lo) {
 #pragma unroll
           for (int i = 0; i < Q; ++i) y[i][0] = mask_infeasible<3>(y[i], a);
         }
-        box_terms3<Q>(y, a.boxes, a.nbox, corner, pos, neg);
+        box_terms3<Q>(y, a.boxes, a.nbox, corner, walk, pos, neg);
       }
     sum[gi] = pos - neg;
   }

@@ -1085,6 +1085,7 @@ __global__ __launch_bounds__(1024) void k_nehvi_ehvi3(NehviEhviArgs a) {
   const int64_t kstride = (int64_t)a.S * a.ldd;
   const int gs = (a.S + kGroups3 - 1) / kGroups3;   // draws per group
   float sum[kGroups3 / 4];                          // this wave's groups (W >= 4)
+  int walk = 0;
   auto load = [&](int s, float (&dv)[Q][3]) {
 #pragma unroll
     for (int k = 0; k < 3; ++k)
@@ -1119,7 +1120,7 @@ __global__ __launch_bounds__(1024) void k_nehvi_ehvi3(NehviEhviArgs a) {
       const float* bx = a.boxes + (int64_t)o0 * 6;
       box_terms3<Q>(y, bx, nbox,
                     [&](int c, int k) { return c < nbox ? bx[6 * c + k] : __builtin_huge_valf(); },
-                    pos, neg);
+                    walk, pos, neg);
     }
     sum[gi] = pos - neg;
   }

@@ -192,6 +192,34 @@ def test_three_objective_infinite_samples(q):
     np.testing.assert_array_equal(e, np.float32(one))
 
 
+def test_three_objective_small_fronts_are_walked():
+    """Where the lanes of a wave are far apart nearly every box is reached, and
+    a front of any size is walked box after box: a box of a front of 23 points
+    (47 boxes, below one 64-box chunk) may not cost 1.3 times one of a front of
+    72 (145 boxes); visited one by one the small front's cost 1.47 times those."""
+    import torch
+    import paper_2602_10729_amd as bo
+    per_box = []
+    for P in (23, 72):
+        _announce("walked front", P)
+        wl = _front_workload(P, 1, 256, 65536)
+        wl.lengthscale[:] = 1.5
+        model = bo.fit(to_dev(wl.X), to_dev(wl.Y), wl.lengthscale, wl.outputscale, wl.noise)
+        cand, Z = to_dev(wl.cand), to_dev(wl.Z)
+        boxes = len(bo.box_decomposition(wl.Y[model.front_indices()], wl.ref)[0])
+        best = np.inf
+        bo.profile_enable(True)
+        for _ in range(10):
+            for _ in range(4):
+                bo.score(model, cand, wl.ref, Z)
+            torch.cuda.synchronize()
+            _, ms, calls, _ = bo.profile_read()
+            best = min(best, ms / calls)
+        bo.profile_enable(False)
+        per_box.append(best / boxes)
+    assert per_box[0] < 1.3 * per_box[1], per_box
+
+
 def test_three_objective_samples_at_the_lds_limit():
     """The largest S of q = 4 with three objectives: the samples leave no room
     in LDS for the boxes' corners, which then come from global memory."""
