@@ -64,8 +64,8 @@ struct Model {
   // fit runs and by every call that uses the model; cleared when the fit has
   // synchronised): releasing then waits for the device first
   bool pending = false;
-  float* Xs = nullptr;           // [m][n_pad][dx] X / lengthscale (fp32)
-  float* invls = nullptr;        // [m][dx] 1 / lengthscale (fp32, 0-padded)
+  float* Xs = nullptr;           // [m][n_pad][dx] X times invls (fp32)
+  float* invls = nullptr;        // [m][dx] 1 / lengthscale (fp32, 0-padded; plain: times kM52Rate)
   float* alpha = nullptr;        // [m][n_pad]
   float* wts = nullptr;          // composite: [m][n_pad] preference weights of X (0 past n)
   float* pref = nullptr;         // composite: [m][d - dr] preference slopes
@@ -82,7 +82,7 @@ struct Model {
   double* ils64 = nullptr;       // [m][d]
   int n_fit = 0;
   uint16_t* xf = nullptr;        // [m][nb][dist_frags(dx)][512] distance fragments of X
-  float* x2 = nullptr;           // [m][2][n_pad] squared norms of the centred rows (plain: halved)
+  float* x2 = nullptr;           // [m][2][n_pad] squared norms of the centred rows
   float* ctr = nullptr;          // [m][dx] centre of the scaled coordinates
 
   // scoring workspace (grown on demand)
@@ -172,7 +172,8 @@ hipError_t launch_mll(const float* X, int64_t n, int d, int m, int nf, const Gra
                       double* A, const double* W, const double* tmp, const double* alpha64,
                       double* partials, double* out, hipStream_t st);
 // The lengthscale-scaled X in the slot layout from the fp64 inverse
-// lengthscales ils [m][d], with the fp32 per-slot values invls [m][dx], the
+// lengthscales ils [m][d] (plain models, dr = 0: times kM52Rate), with the fp32
+// per-slot values invls [m][dx], the
 // copy Xd [n][d] of X, (composite, pref non-NULL) the fp32 preference slopes
 // pref [m][d - dr] from their fp64 copies pref_d, and (ils64 non-NULL) a copy
 // of ils.
@@ -180,30 +181,41 @@ hipError_t launch_scale_x(const float* X, int64_t n, int d, int m, int nb, int d
                           int dr4, const double* ils, float* invls, const double* pref_d,
                           float* pref, float* Xd, double* ils64, float* Xs, hipStream_t st);
 
+// Plain models scale the coordinates by sqrt5 log2(e) / lengthscale, so that a
+// scaled distance t = sqrt5 log2(e) r is the exponent of two itself:
+// M52 = (1 + ln2 t + (ln2 t)^2 / 3) 2^-t. No constant of the exponent is rounded
+// then (in r^2 it is 3.5e-8 low, in r^2 / 2 3.4e-8 high, the same way for
+// every pair), and ln2 is an fp32 number within 2.8e-9.
+constexpr double kM52Rate = 2.23606797749978969641 * 1.44269504088896340736;
+constexpr float kM52t = 0.69314718055994530942f, kM52t2 = 0.16015100463940045f;   // ln2, ln2^2 / 3
+// A pair closer than r = 1 (see Producer) is closer than t = kM52Rate.
+constexpr float kNear = static_cast<float>(kM52Rate * kM52Rate);
+
 // Squared distances in the posterior kernel come from the expansion
 // |c|^2 + |x|^2 - 2 c.x of centred scaled coordinates, with c.x on the fp16
-// matrix cores: each value splits into hi = fp16(v) and lo = fp16(2^11 (v -
+// matrix cores: each value splits into hi = fp16(v) and lo = fp16(2^b (v -
 // hi)); stream 0 pairs x_hi with c_hi over the D = dx slots, stream 1 x_lo
 // with c_hi and x_hi with c_lo over 2D positions. Fragments of 32 k-positions
 // per 16-row group: stream 0 first, then stream 1.
-// Plain models accumulate h = r^2 / 2 in one chain that starts from
-// (|c|^2 + |x|^2) / 2, the candidate's halves negated, and stream 1's high
-// halves (x's and c's) scaled by 2^-11 so that its terms have stream 0's
-// scale: half as many vector operations per pair as two accumulators. The
-// scaled halves may be fp16 subnormals; what they lose is below
-// 2^-26 (|c| + |x|), and pairs with r^2 < 1 are recomputed exactly.
-// Composite models keep two accumulators, c.x = acc0 + 2^-11 acc1, unscaled
-// halves and whole norms: the one-chain form was 3% faster there too, but it
-// moves the means by 1e-6, and under feasibility thresholds a sample that
-// changes side moves an acquisition value by up to 5% of their rms.
+// Plain models accumulate c.x in one chain, the small stream 1 first, its high
+// halves (x's and c's) scaled by 2^-b so that its terms have stream 0's scale.
+// b = 6, about half of the 11 bits between the halves, so that both operands
+// stay clear of the fp16 subnormals alike: a value v loses bits only below
+// 2^-8, and each term then at most 2^-30 of its partner (b = 11: 2^-25), in
+// the sum below half an fp32 ulp of |c|^2 + |x|^2 for the pairs with r^2 >= 1
+// (the others are recomputed exactly).
+// Composite models keep two accumulators, c.x = acc0 + 2^-11 acc1, with b = 11
+// and unscaled high halves: one chain there moves the means in their last
+// digits, and under feasibility thresholds a sample that changes side moves an
+// acquisition value by up to 5% of their rms.
 __host__ __device__ constexpr int dist_frags0(int dx) { return (dx + 31) / 32; }
 __host__ __device__ constexpr int dist_frags(int dx) { return (dx + 31) / 32 + (2 * dx + 31) / 32; }
-constexpr float kDistLoScale = 2048.0f;
+constexpr float kDistLoScale = 64.0f, kDistLoScaleComp = 2048.0f;   // 2^b
 
 // Centre the scaled coordinates (ctr = mean over the n rows), then write the
 // A fragments of the centred rows (xf, zero for rows past n) and their
 // squared norms per coordinate group (x2 [2][n_pad]: routing slots t < 4*dr4,
-// then the rest; a plain model has everything, halved, in the second group).
+// then the rest; a plain model has everything in the second group).
 hipError_t launch_pack_x(const float* Xs, int64_t n, int m, int nb, int dx, int dr4,
                          float* ctr, uint16_t* xf, float* x2, hipStream_t st);
 
@@ -286,7 +298,7 @@ struct NehviMeansArgs {
   const float* invls;      // [m][dx]
   const uint16_t* xf;      // [m][xf_stride] centred-X distance fragments (fp16 bits)
   int64_t xf_stride;
-  const float* x2;         // [m][2][n_pad] squared norms of the centred rows per group (plain: halved)
+  const float* x2;         // [m][2][n_pad] squared norms of the centred rows per group
   const float* ctr;        // [m][dx] centre of the scaled coordinates
   const uint16_t* Gp;      // packed G^T fragments (fp16 bits)
   float s[3];              // output scales (composite: of the routing term)
@@ -353,7 +365,7 @@ struct PosteriorArgs {
   // split scale 2^(14 - E) (s = f 2^E, f in [0.5, 1)), and 2^(E - 14)
   float ss, kinv0;
   const uint16_t* xf;  // [nb][dist_frags(dx)][512] centred-X distance fragments
-  const float* x2;     // [2][n_pad] squared norms of the centred rows per coordinate group (plain: halved)
+  const float* x2;     // [2][n_pad] squared norms of the centred rows per coordinate group
   const float* ctr;    // [dx] centre subtracted from the scaled coordinates
   int n, nb;
   float s;             // output scale (composite: of the routing term)

@@ -775,15 +775,16 @@ __global__ __launch_bounds__(256) void k_pack(const double* __restrict__ W, int6
 }
 
 // Xs[k][i][t] = X[i][slot_dim(t)] * invls[k][t] (zero for padding slots and
-// rows beyond n), with invls[k][t] = fp32(ils[k][slot_dim(t)]) also written
-// out (the fp64 inverse lengthscale rounded to fp32 is the fp32 quotient
-// 1 / lengthscale: double rounding is exact for a quotient when the wider
-// format has at least 2p + 2 bits). Objective 0 also copies X into Xd;
+// rows beyond n), with invls[k][t] = fp32(rate ils[k][slot_dim(t)]) also written
+// out (plain: rate = kM52Rate; composite: 1, and the fp64 inverse lengthscale
+// rounded to fp32 is the fp32 quotient 1 / lengthscale: double rounding is exact
+// for a quotient when the wider format has at least 2p + 2 bits). Objective 0
+// also copies X into Xd;
 // (composite) fp32 preference slopes come from their fp64 copies, and (fp64
 // scoring) ils is copied into ils64.
 __global__ __launch_bounds__(256) void k_scale_x(const float* __restrict__ X, int64_t n,
                                                  int d, int dx, int dr, int dr4, int n_pad,
-                                                 const double* __restrict__ ils,
+                                                 const double* __restrict__ ils, double rate,
                                                  float* __restrict__ invls,
                                                  const double* __restrict__ pref_d,
                                                  float* __restrict__ pref, int dc,
@@ -796,7 +797,7 @@ __global__ __launch_bounds__(256) void k_scale_x(const float* __restrict__ X, in
   const int64_t i = e / dx;
   const int t = static_cast<int>(e % dx);
   const int c = slot_dim(t, d, dr, dr4);
-  const float il = (c >= 0) ? static_cast<float>(ils[k * d + c]) : 0.f;
+  const float il = (c >= 0) ? static_cast<float>(rate * ils[k * d + c]) : 0.f;
   float v = 0.f;
   if (i < n && c >= 0) v = X[i * d + c] * il;
   Xs[(int64_t)k * n_pad * dx + e] = v;
@@ -828,12 +829,13 @@ __global__ __launch_bounds__(256) void k_center_x(const float* __restrict__ Xs, 
 // One thread per (row group g, fragment f, lane l): the eight fp16 values of
 // the A fragment of v_mfma_f32_16x16x32_f16 that lane l supplies (row 16g +
 // l%16, positions 8(l/16) .. +7 of the fragment's 32), from the centred row
-// xc = Xs - ctr: stream 0 holds hi(xc[p]) at p < dx, stream 1 lo(xc[p]) at
-// p < dx and hi1 hi(xc[p - dx]) at dx <= p < 2dx (hi1 = 1 for composite
-// models, else 2^-11: dist_frags); zero elsewhere and for rows past n.
+// xc = Xs - ctr: stream 0 holds hi(xc[p]) at p < dx, stream 1 lo(xc[p]), scaled
+// by lo1, at p < dx and hi1 hi(xc[p - dx]) at dx <= p < 2dx (lo1 = 2^11,
+// hi1 = 1 for composite models, else 2^6 and 2^-6: dist_frags); zero elsewhere
+// and for rows past n.
 __global__ __launch_bounds__(256) void k_pack_x(const float* __restrict__ Xs, int64_t n,
                                                 int n_pad, int nb, int dx,
-                                                const float* __restrict__ ctr, float hi1,
+                                                const float* __restrict__ ctr, float lo1, float hi1,
                                                 _Float16* __restrict__ xf) {
   const int k = blockIdx.y;
   const int nf = dist_frags(dx), f0 = dist_frags0(dx);
@@ -855,7 +857,7 @@ __global__ __launch_bounds__(256) void k_pack_x(const float* __restrict__ Xs, in
       } else if (p < dx) {
         const float xc = x[p] - c[p];
         const _Float16 h = static_cast<_Float16>(xc);
-        v = static_cast<_Float16>((xc - static_cast<float>(h)) * kDistLoScale);
+        v = static_cast<_Float16>((xc - static_cast<float>(h)) * lo1);
       } else if (p < 2 * dx) {
         v = static_cast<_Float16>(x[p - dx] - c[p - dx]) * static_cast<_Float16>(hi1);
       }
@@ -865,8 +867,7 @@ __global__ __launch_bounds__(256) void k_pack_x(const float* __restrict__ Xs, in
 }
 
 // x2[k][0][i] = sum over routing slots (t < 4*dr4) of (Xs - ctr)^2, x2[k][1][i]
-// over the others (half of it for a plain model, dr4 = 0), both fp32 in slot
-// order; zero for rows past n
+// over the others, both fp32 in slot order; zero for rows past n
 __global__ __launch_bounds__(256) void k_norm_x(const float* __restrict__ Xs, int64_t n,
                                                 int n_pad, int dx, int dr4,
                                                 const float* __restrict__ ctr,
@@ -885,7 +886,7 @@ __global__ __launch_bounds__(256) void k_norm_x(const float* __restrict__ Xs, in
     }
   }
   x2[((int64_t)k * 2 + 0) * n_pad + i] = g0;
-  x2[((int64_t)k * 2 + 1) * n_pad + i] = (dr4 > 0) ? g1 : 0.5f * g1;
+  x2[((int64_t)k * 2 + 1) * n_pad + i] = g1;
 }
 
 // ---- log marginal likelihood and its gradient ------------------------------
@@ -1202,7 +1203,7 @@ hipError_t launch_scale_x(const float* X, int64_t n, int d, int m, int nb, int d
   const int n_pad = nb * kBlk;
   const unsigned gx2 = static_cast<unsigned>(((int64_t)n_pad * dx + 255) / 256);
   hipLaunchKernelGGL(k_scale_x, dim3(gx2, m), dim3(256), 0, st, X, n, d, dx, dr, dr4, n_pad,
-                     ils, invls, pref_d, pref, d - dr, Xd, ils64, Xs);
+                     ils, dr > 0 ? 1.0 : kM52Rate, invls, pref_d, pref, d - dr, Xd, ils64, Xs);
   return hipGetLastError();
 }
 
@@ -1213,8 +1214,8 @@ hipError_t launch_pack_x(const float* Xs, int64_t n, int m, int nb, int dx, int 
   hipLaunchKernelGGL(k_center_x, dim3(dx, m), dim3(256), 0, st, Xs, n, n_pad, dx, ctr);
   const int64_t th = (int64_t)nb * dist_frags(dx) * 64;
   hipLaunchKernelGGL(k_pack_x, dim3(static_cast<unsigned>((th + 255) / 256), m), dim3(256), 0, st,
-                     Xs, n, n_pad, nb, dx, ctr, dr4 > 0 ? 1.0f : 1.0f / kDistLoScale,
-                     reinterpret_cast<_Float16*>(xf));
+                     Xs, n, n_pad, nb, dx, ctr, dr4 > 0 ? kDistLoScaleComp : kDistLoScale,
+                     dr4 > 0 ? 1.0f : 1.0f / kDistLoScale, reinterpret_cast<_Float16*>(xf));
   hipLaunchKernelGGL(k_norm_x, dim3(static_cast<unsigned>((n_pad + 255) / 256), m), dim3(256), 0,
                      st, Xs, n, n_pad, dx, dr4, ctr, x2);
   return hipGetLastError();

@@ -482,13 +482,11 @@ __device__ __forceinline__ float m52(float r2, float s) {
   return s * fmaf(r, 2.23606798f, fmaf(r2, 1.66666667f, 1.0f)) * e;
 }
 
-// Matern-5/2 from half the squared scaled distance h = r^2 / 2, u = sqrt(h):
-// s (1 + sqrt10 u + 10/3 h) exp(-sqrt10 u), su = s sqrt10, sh = s 10/3.
-constexpr float kM52u = 3.16227766f, kM52h = 3.33333333f;
-__device__ __forceinline__ float m52h(float h, float s, float su, float sh) {
-  const float u = __builtin_amdgcn_sqrtf(h);
-  constexpr float kNegSqrt10Log2e = static_cast<float>(-3.16227766016837933200 * 1.44269504088896340736);
-  return fmaf(u, su, fmaf(h, sh, s)) * __builtin_amdgcn_exp2f(kNegSqrt10Log2e * u);
+// s M52 of a plain model's squared distance t^2 (kM52Rate): s1 = s ln2,
+// s2 = s ln2^2 / 3.
+__device__ __forceinline__ float m52t(float t2, float s, float s1, float s2) {
+  const float t = __builtin_amdgcn_sqrtf(t2);
+  return fmaf(t, s1, fmaf(t2, s2, s)) * __builtin_amdgcn_exp2f(-t);
 }
 
 constexpr int kMW = 8;                 // waves per workgroup
@@ -519,8 +517,8 @@ template <int DX4, int CB, bool COMP>
 __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
   constexpr int RS = 4 * DX4;
   constexpr int NS = COMP ? 2 : 1;
-  constexpr int NF = dist_frags(RS);
-  static_assert(dist_frags0(RS) == 1 && NF <= 3, "at most 32 coordinate slots");
+  constexpr int F0 = dist_frags0(RS), NF = dist_frags(RS);
+  static_assert(F0 == 1 && NF <= 3, "at most 32 coordinate slots");
   static_assert(2 * kMT * 96 <= 3 * kRingSlot, "candidate fragments fit the ring");
   __shared__ __align__(16) _Float16 ring[3 * kRingSlot];
   __shared__ __align__(16) float ctile[kMT * RS];   // exact scaled candidates
@@ -580,7 +578,7 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
   // centred coordinates: squared norms per group, and the B fragments of the
   // distance MFMAs, staged in the (not yet used) ring as 96 halves per group
   // and column: [0, 32) stream 0 (hi, zero past RS), [32, 96) stream 1 (hi at
-  // p < RS, 2^11-scaled lo at RS <= p < 2RS, zero beyond)
+  // p < RS, scaled lo at RS <= p < 2RS, zero beyond)
   float c2[NS];
   halfx8 cb[NS][NF];
   {
@@ -595,7 +593,7 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
         const bool in = !COMP || ((t < 4 * a.dr4) == (g == 0));
         if (in) n2 = fmaf(ct[t], ct[t], n2);
       }
-      c2[g] = COMP ? n2 : 0.5f * n2;
+      c2[g] = n2;
     }
     if (half == 0 && (lane >> 4) == 0) {
 #pragma unroll
@@ -609,11 +607,11 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
           const bool in = !COMP || ((t < 4 * a.dr4) == (g == 0));
           const _Float16 hi = static_cast<_Float16>(in ? ct[t] : 0.f);
           const _Float16 lo = static_cast<_Float16>(
-              in ? (ct[t] - static_cast<float>(static_cast<_Float16>(ct[t]))) * kDistLoScale : 0.f);
-          v[t / 8][t % 8] = COMP ? hi : -hi;
+              in ? (ct[t] - static_cast<float>(hi)) * (COMP ? kDistLoScaleComp : kDistLoScale) : 0.f);
+          v[t / 8][t % 8] = hi;
           v[(32 + t) / 8][(32 + t) % 8] =
-              COMP ? hi : -hi * static_cast<_Float16>(1.0f / kDistLoScale);
-          v[(32 + RS + t) / 8][(32 + RS + t) % 8] = COMP ? lo : -lo;
+              COMP ? hi : hi * static_cast<_Float16>(1.0f / kDistLoScale);
+          v[(32 + RS + t) / 8][(32 + RS + t) % 8] = lo;
         }
 #pragma unroll
         for (int i = 0; i < 12; ++i) *reinterpret_cast<halfx8*>(h + 8 * i) = v[i];
@@ -652,7 +650,6 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
     bool ex[4];
     bool any = false;
     if constexpr (COMP) {
-      constexpr int F0 = dist_frags0(RS);
       floatx4 d0[NS], d1[NS];
 #pragma unroll
       for (int g = 0; g < NS; ++g) {
@@ -671,7 +668,7 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
 #pragma unroll
         for (int g = 0; g < NS; ++g) {
           const float nrm = c2[g] + x2v[g][e];
-          const float dot = fmaf(d1[g][e], 1.0f / kDistLoScale, d0[g][e]);
+          const float dot = fmaf(d1[g][e], 1.0f / kDistLoScaleComp, d0[g][e]);
           dist[g][e] = fmaxf(fmaf(-2.0f, dot, nrm), 0.f);
           rt += dist[g][e];
           nt += nrm;
@@ -680,17 +677,18 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
         any = any || ex[e];
       }
     } else {
-      floatx4 dd;
-      float hn[4];
+      floatx4 dd = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) dd[e] = hn[e] = c2[0] + x2v[0][e];
+      for (int f = F0; f < NF; ++f)
+        dd = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f], cb[0][f], dd, 0, 0, 0);
 #pragma unroll
-      for (int f = 0; f < NF; ++f)
+      for (int f = 0; f < F0; ++f)
         dd = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa[f], cb[0][f], dd, 0, 0, 0);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        dist[0][e] = dd[e];
-        ex[e] = !(dd[e] >= fmaf(hn[e], 1.0f / 256.0f, 0.5f));
+        const float nrm = c2[0] + x2v[0][e];
+        dist[0][e] = fmaf(-2.0f, dd[e], nrm);
+        ex[e] = !(dist[0][e] >= fmaf(nrm, 1.0f / 256.0f, kNear));
         any = any || ex[e];
       }
     }
@@ -716,7 +714,7 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
           else s1 += t;
         }
         if (ex[e]) {
-          dist[0][e] = COMP ? s0 : 0.5f * s1;
+          dist[0][e] = COMP ? s0 : s1;
           if constexpr (COMP) dist[NS - 1][e] = s1;
         }
       }
@@ -731,7 +729,7 @@ __global__ __launch_bounds__(kMW * 64) void k_nehvi_means(NehviMeansArgs a) {
         const float k3 = m32(dist[NS - 1][e]);
         kv = fmaf(wsd * wtv[e], k3, k5 * fmaf(sints, k3, sks));
       } else {
-        kv = m52h(dist[0][e], sks, sks * kM52u, sks * kM52h);
+        kv = m52t(dist[0][e], sks, sks * kM52t, sks * kM52t2);
       }
       // one fp32 value for both halves (the compiler may otherwise fuse the
       // last product into the fp16 conversions and derive the high half twice)

@@ -106,6 +106,7 @@ constexpr int kRing = 16;                   // K*^T blocks held in LDS
 constexpr int kG = 4;                       // steps per barrier while producing
 constexpr int kCSH = kRing * kJ + 8;        // ring column stride in halves (260 dwords)
 
+// Matern correlations of a squared scaled distance r^2 (composite kernel).
 __device__ __forceinline__ float matern52_f(float r2, float s) {
   const float r = __builtin_amdgcn_sqrtf(r2);
   // exp(-sqrt5 r) = 2^(-sqrt5 log2(e) r)
@@ -123,15 +124,13 @@ __device__ __forceinline__ float matern32_f(float r2) {
   return fmaf(r, 1.73205081f, 1.0f) * __builtin_amdgcn_exp2f(kNegSqrt3Log2e * r);
 }
 
-// Matern-5/2 from half the squared scaled distance h = r^2 / 2, u = sqrt(h):
-// s (1 + sqrt10 u + 10/3 h) exp(-sqrt10 u), with su = s sqrt10 and
-// sh = s 10/3 given.
-constexpr float kM52u = 3.16227766f, kM52h = 3.33333333f;
-__device__ __forceinline__ float matern52_h(float h, float s, float su, float sh) {
-  constexpr float kNegSqrt10Log2e = static_cast<float>(-3.16227766016837933200 * 1.44269504088896340736);
-  const float u = __builtin_amdgcn_sqrtf(h);
-  return fmaf(u, su, fmaf(h, sh, s)) * __builtin_amdgcn_exp2f(kNegSqrt10Log2e * u);
+// s M52 of a plain model's squared distance t^2 (kM52Rate), with s1 = s ln2 and
+// s2 = s ln2^2 / 3 given.
+__device__ __forceinline__ float matern52_t(float t2, float s, float s1, float s2) {
+  const float t = __builtin_amdgcn_sqrtf(t2);
+  return fmaf(t, s1, fmaf(t2, s2, s)) * __builtin_amdgcn_exp2f(-t);
 }
+
 __device__ __forceinline__ float quad_xor(float v, int x) {
   // DPP quad_perm: lane i of each group of 4 reads lane i ^ x.
   int iv = __float_as_int(v);
@@ -172,10 +171,12 @@ typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
 // lane l holds column 16(w%4) + l%16 and rows 16(w/4) + 4(l/16) .. +3.
 //
 // Squared distances: r^2 = |c|^2 + |x|^2 - 2 c.x over coordinates centred on
-// the training mean, c.x on the matrix cores from fp16 hi and 2^11-scaled lo
-// halves (the fit packs the rows, the kernel the candidates; see dist_frags).
-// A plain model's chain of MFMAs starts from (|c|^2 + |x|^2) / 2 and leaves
-// h = r^2 / 2, which the Matern evaluation takes as it is. Where the expansion
+// the training mean, c.x on the matrix cores from fp16 hi and scaled lo halves
+// (the fit packs the rows, the kernel the candidates; see dist_frags), in one
+// accumulator for plain models, stream 1 first, in two for composite ones. (A
+// plain model's r^2 here is t^2, see kM52Rate. A chain that starts from the norms
+// saves an operation per pair, but rounds at their size at each link and drops
+// cross terms below half their ulp: r^2 4-8% further off.) Where the expansion
 // can cancel badly, i.e. for a pair whose approximate r^2 is below
 // 1 + (|c|^2 + |x|^2)/256, the pair is recomputed from exact differences of
 // the scaled coordinates: near a training point k(x*, x_i) is close to its
@@ -225,18 +226,17 @@ __device__ __forceinline__ void prod_load(Producer<NT, DX4, COMP>& P, int n_pad,
 }
 
 // Squared scaled distances of this lane's four rows of the block whose
-// operands prod_load fetched, by the expansion: dist[0] = r^2 / 2 (plain) or
-// the groups' r^2 (composite). ex marks the pairs to recompute exactly, any
+// operands prod_load fetched, by the expansion: dist[0] (composite: each
+// group's). ex marks the pairs to recompute exactly, any
 // whether there is one. Reads the operands' distance part only (xa, x2).
 template <int NT, int DX4, bool COMP>
 __device__ __forceinline__ void produce_dist(const Producer<NT, DX4, COMP>& P,
                                              float (&dist)[Producer<NT, DX4, COMP>::NS][4],
                                              bool (&ex)[4], bool& any) {
   using Pr = Producer<NT, DX4, COMP>;
-  constexpr int NS = Pr::NS, NF = Pr::NF;
+  constexpr int NS = Pr::NS, F0 = Pr::F0, NF = Pr::NF;
   any = false;
   if constexpr (COMP) {
-    constexpr int F0 = Pr::F0;
     floatx4 d0[NS], d1[NS];
 #pragma unroll
     for (int g = 0; g < NS; ++g) {
@@ -255,7 +255,7 @@ __device__ __forceinline__ void produce_dist(const Producer<NT, DX4, COMP>& P,
 #pragma unroll
       for (int g = 0; g < NS; ++g) {
         const float nrm = P.c2[g] + P.x2[g][e];
-        const float dot = fmaf(d1[g][e], 1.0f / kDistLoScale, d0[g][e]);
+        const float dot = fmaf(d1[g][e], 1.0f / kDistLoScaleComp, d0[g][e]);
         dist[g][e] = fmaxf(fmaf(-2.0f, dot, nrm), 0.f);
         rt += dist[g][e];
         nt += nrm;
@@ -264,18 +264,19 @@ __device__ __forceinline__ void produce_dist(const Producer<NT, DX4, COMP>& P,
       any = any || ex[e];
     }
   } else {
-    floatx4 d;
-    float hn[4];
+    floatx4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) d[e] = hn[e] = P.c2[0] + P.x2[0][e];
+    for (int f = F0; f < NF; ++f)
+      d = __builtin_amdgcn_mfma_f32_16x16x32_f16(P.xa[f], P.cb[0][f], d, 0, 0, 0);
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
+    for (int f = 0; f < F0; ++f)
       d = __builtin_amdgcn_mfma_f32_16x16x32_f16(P.xa[f], P.cb[0][f], d, 0, 0, 0);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      dist[0][e] = d[e];
+      const float nrm = P.c2[0] + P.x2[0][e];
+      dist[0][e] = fmaf(-2.0f, d[e], nrm);
       // (a NaN, from fp16 overflow, is near too)
-      ex[e] = !(d[e] >= fmaf(hn[e], 1.0f / 256.0f, 0.5f));
+      ex[e] = !(dist[0][e] >= fmaf(nrm, 1.0f / 256.0f, kNear));
       any = any || ex[e];
     }
   }
@@ -309,7 +310,7 @@ __device__ __forceinline__ void exact_dist(Producer<NT, DX4, COMP>& P, const Pos
         else s1 += t;
       }
       if (ex[e]) {
-        dist[0][e] = COMP ? s0 : 0.5f * s1;
+        dist[0][e] = COMP ? s0 : s1;
         if constexpr (COMP) dist[Pr::NS - 1][e] = s1;
       }
     }
@@ -338,7 +339,7 @@ __device__ __forceinline__ void produce_kv(Producer<NT, DX4, COMP>& P, const Pos
       const float k3 = matern32_f(dist[1][e]);
       kv = fmaf(P.wsd * wt[e], k3, k5 * fmaf(P.sis, k3, P.ss));
     } else {
-      kv = matern52_h(dist[0][e], a.ss, a.ss * kM52u, a.ss * kM52h);
+      kv = matern52_t(dist[0][e], a.ss, a.ss * kM52t, a.ss * kM52t2);
     }
     // kv is rounded to fp32 here, once: otherwise the compiler may fuse its
     // last product into the fp16 conversions and derive the high half twice
@@ -634,7 +635,7 @@ __global__ __launch_bounds__(kThreads) void k_posterior(PosteriorBatch batch) {
         const bool in = !COMP || ((t < 4 * a.dr4) == (g == 0));
         if (in) n2 = fmaf(ct[t], ct[t], n2);
       }
-      P.c2[g] = COMP ? n2 : 0.5f * n2;
+      P.c2[g] = n2;
     }
     // a candidate with a non-finite coordinate: its unscale factor is NaN, so
     // its mu and variance read NaN (the hot loop's clamps would hide it)
@@ -652,11 +653,11 @@ __global__ __launch_bounds__(kThreads) void k_posterior(PosteriorBatch batch) {
           const bool in = !COMP || ((t < 4 * a.dr4) == (g == 0));
           const _Float16 hi = static_cast<_Float16>(in ? ct[t] : 0.f);
           const _Float16 lo = static_cast<_Float16>(
-              in ? (ct[t] - static_cast<float>(static_cast<_Float16>(ct[t]))) * kDistLoScale : 0.f);
-          v[t / 8][t % 8] = COMP ? hi : -hi;
+              in ? (ct[t] - static_cast<float>(hi)) * (COMP ? kDistLoScaleComp : kDistLoScale) : 0.f);
+          v[t / 8][t % 8] = hi;
           v[(32 + t) / 8][(32 + t) % 8] =
-              COMP ? hi : -hi * static_cast<_Float16>(1.0f / kDistLoScale);
-          v[(32 + D + t) / 8][(32 + D + t) % 8] = COMP ? lo : -lo;
+              COMP ? hi : hi * static_cast<_Float16>(1.0f / kDistLoScale);
+          v[(32 + D + t) / 8][(32 + D + t) % 8] = lo;
         }
 #pragma unroll
         for (int i = 0; i < 12; ++i) *reinterpret_cast<halfx8*>(h + 8 * i) = v[i];
@@ -714,7 +715,7 @@ __global__ __launch_bounds__(kThreads) void k_posterior(PosteriorBatch batch) {
         const float k3 = matern32_f(r2);
         kpp[P.col * 4 + x] = fmaf(a.s_dep * wstar * wm, k3, k5 * fmaf(a.s_int, k3, a.s));
       } else {
-        kpp[P.col * 4 + x] = matern52_f(r2, a.s);
+        kpp[P.col * 4 + x] = matern52_t(r2, a.s, a.s * kM52t, a.s * kM52t2);
       }
     }
   }

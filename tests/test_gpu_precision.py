@@ -212,3 +212,61 @@ def test_nan_candidate_gives_nan_and_never_wins(q):
     assert_close(g["ehvi"][ok], o["ehvi"], TOL_EHVI, f"ehvi beside NaN q={q}")
     assert g["idx"] not in bad
     check_argmax(g["idx"], o["ehvi"], idx_pool=ok)
+
+
+def _far_pair_error(X, ls, cand):
+    """Relative error of mu where one observation alone carries it: the error
+    of its kernel value, for candidates far from it (no exact differences)."""
+    M = len(cand)
+    wl = bi.make_config(0, seed=0, M=M)
+    wl.X, wl.n, wl.d = X, 2, X.shape[1]
+    wl.Y = np.array([[1, 1], [0, 0]], np.float32)
+    wl.lengthscale = np.stack([ls, ls]).astype(np.float32)
+    wl.outputscale, wl.noise = np.ones(2, np.float32), np.full(2, 1e-4, np.float32)
+    wl.cand = np.ascontiguousarray(cand.reshape(M, 1, -1), dtype=np.float32)
+    wl.Z = wl.Z[:4].copy()
+    wl.ref = np.array([-1, -1], np.float32)
+    g, o = gpu_run(wl), oracle_score(oracle_fit(wl), wl)
+    return (g["mu"][:, 0, 0] - o["mu"][:, 0, 0]) / o["mu"][:, 0, 0]
+
+
+def test_small_cross_terms_count():
+    """The products of a large coordinate's low half with a small one reach r^2.
+    x = +-(1 + 2^-11) in each of 32 dimensions, candidates c in [0, 2^-12]: those
+    products add up to 32 * 2^-11 * 2^-13 = 1.9e-6, half an fp32 ulp of the norms
+    (33), so an accumulator that already holds the norms loses them. Then r^2 is
+    off by +-3.8e-6 for c and -c and the kernel values (r = 5.7: |d ln k / d r^2|
+    = 0.17) by 1.3e-6 against each other. The roundings of r^2 and k, 5e-7 a
+    value, are another for every candidate: the mean difference over 8192 of
+    each sign is 8e-9 by their spread, and below 4e-8 where c or x have other
+    sizes (the errors of the hardware's sqrt and exp2 are no pure noise)."""
+    r = np.random.default_rng(3)
+    x = np.full((1, 32), 1 + 0.499 * 2.0 ** -10, np.float32)
+    c = (2.0 ** -12 * r.random((8192, 32))).astype(np.float32)
+    _announce("small cross terms")
+    e = _far_pair_error(np.concatenate([x, -x]), np.ones(32), np.concatenate([c, -c]))
+    diff = float(np.mean(e[:8192] - e[8192:]))
+    log_ratio("small cross terms, mean difference", abs(diff) / 2e-7)
+    assert abs(diff) < 2e-7, diff
+
+
+def test_kernel_values_carry_no_common_error():
+    """A rounded constant in the exponent moves every kernel value the same
+    way: 3.4e-8 of the exponent sqrt5 r is 2.3e-7 of k at r = 3. Candidates at
+    r = 2.5 .. 3.5 of one observation (the other far away: its norm asks for
+    exact differences everywhere), 16 different lengthscales. The fp32 rates of
+    the coordinates are each within 2^-24, in rms below 2^-24 / sqrt3 and
+    independent, so r within 2^-24 / sqrt3 / sqrt16 = 8.6e-9 and k (|d ln k / d ln
+    r| = 5.1 at r = 3) within 4.4e-8: twice that, and 1e-8 for the constants of
+    the polynomial (ln2, ln2^2 / 3 and their products with the scale)."""
+    r = np.random.default_rng(4)
+    ls = (0.5 + r.random(16)).astype(np.float32)
+    u = r.standard_normal((8192, 16))
+    u *= (2.5 + r.random((8192, 1))) / np.linalg.norm(u, axis=1, keepdims=True)
+    x = (0.2 * r.standard_normal(16)).astype(np.float32)
+    far = (x + 20.0 * ls).astype(np.float32)
+    _announce("common error")
+    e = _far_pair_error(np.stack([x, far]), ls, x + u * ls)
+    mean = float(np.mean(e))
+    log_ratio("kernel values, mean relative error", abs(mean) / 1e-7)
+    assert abs(mean) < 1e-7, mean
