@@ -314,12 +314,15 @@ __global__ __launch_bounds__(kThreads) void k_ehvi_q(EhviArgs a) {
 // boxes are culled per wave (hvi_cull.h). Lanes past the batch sit at -inf.
 // Bound by vector and scalar issue. Against testing box after box in chunks of
 // 2 to 16 samples (the two-objective kernels' way): 131072 batches of 4, 512
-// samples, 235 boxes 11.15 -> 1.76 ms; 33331 pairs, 300 samples, 137 boxes,
-// constrained 0.80 -> 0.13 ms; 65536 single points, 512 samples 2.18 -> 0.25 ms;
-// where every candidate differs (3 dimensions, 143 boxes, 256 samples) 65536
-// single points 0.67 -> 0.68 ms, 16384 batches of 4 3.00 -> 1.03 ms.
+// samples, 235 boxes 10.40 -> 2.03 ms; 33331 pairs, 300 samples, 137 boxes,
+// constrained 1.14 -> 0.185 ms; 256 samples, 6 dimensions, lengthscales 0.3 and
+// 1.5 (the latter: small variances, candidates far apart), 145 boxes: 65536
+// single points 0.65 -> 0.50 and 0.65 -> 0.58 ms, 32768 pairs 1.33 -> 0.48 and
+// 1.36 -> 0.53, 16384 batches of 4 2.93 -> 0.88 and 3.05 -> 1.06; 3 boxes 51 -> 29
+// and 49 -> 28 us, 36 -> 22 and 39 -> 22, 68 -> 58 and 79 -> 61.
 template <int Q, bool CONS>
-__global__ __launch_bounds__(1024) void k_ehvi3(EhviArgs a, bool lds_lo) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80)))
+void k_ehvi3(EhviArgs a, bool lds_lo) {
   extern __shared__ float sm[];
   constexpr int T = Q * (Q + 1) / 2;
   const int nt = blockDim.x, W = nt / 64;
@@ -333,9 +336,13 @@ __global__ __launch_bounds__(1024) void k_ehvi3(EhviArgs a, bool lds_lo) {
       ls[i] = c < a.nbox ? a.boxes[6 * c + k] : __builtin_huge_valf();
     }
   __syncthreads();
-  auto corner = [&](int c, int k) {
-    if (lds_lo) return ls[k * nb64 + c];
-    return c < a.nbox ? a.boxes[6 * c + k] : __builtin_huge_valf();
+  auto corner = [&](int c, float (&l)[3]) {
+    if (lds_lo) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) l[k] = ls[k * nb64 + c];
+    } else {
+      load_corner(a.boxes, a.nbox, c, l);
+    }
   };
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -359,32 +366,33 @@ __global__ __launch_bounds__(1024) void k_ehvi3(EhviArgs a, bool lds_lo) {
       nan_in = nan_in || (C[k][e] != C[k][e]);
     }
   const int gs = (a.S + kGroups - 1) / kGroups;      // samples per group
-  float sum[kGroups / 4];                            // this wave's groups (W >= 4)
-  int walk = 0;
-#pragma unroll
-  for (int gi = 0; gi < kGroups / 4; ++gi) {
+  float sum[kGroups / 4] = {};                       // this wave's groups (W >= 4)
+  CullState cull;
+#pragma unroll 1                                     // one copy of the boxes' code
+  for (int gi = 0; gi < kGroups / W; ++gi) {
     const int g = wave * (kGroups / W) + gi;
-    float pos = 0.f, neg = 0.f;
-    if (gi < kGroups / W)
-      for (int s = g * gs; s < min(a.S, (g + 1) * gs); ++s) {
-        float y[Q][3];
+    HviSums<Q> h;
+    for (int s = g * gs; s < min(a.S, (g + 1) * gs); ++s) {
+      float y[Q][3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
+      for (int k = 0; k < 3; ++k)
 #pragma unroll
-          for (int i = 0; i < Q; ++i) {
-            float v = mu[i][k];
+        for (int i = 0; i < Q; ++i) {
+          float v = mu[i][k];
 #pragma unroll
-            for (int t = 0; t <= i; ++t)
-              v = fmaf(C[k][i * (i + 1) / 2 + t], zs[(s * Q + t) * 3 + k], v);
-            y[i][k] = v;
-          }
-        if constexpr (CONS) {
-#pragma unroll
-          for (int i = 0; i < Q; ++i) y[i][0] = mask_infeasible<3>(y[i], a);
+          for (int t = 0; t <= i; ++t)
+            v = fmaf(C[k][i * (i + 1) / 2 + t], zs[(s * Q + t) * 3 + k], v);
+          y[i][k] = v;
         }
-        box_terms3<Q>(y, a.boxes, a.nbox, corner, walk, pos, neg);
+      if constexpr (CONS) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) y[i][0] = mask_infeasible<3>(y[i], a);
       }
-    sum[gi] = pos - neg;
+      box_terms3<Q>(y, a.boxes, a.nbox, corner, cull, h);
+    }
+    const float t = h.total();
+#pragma unroll
+    for (int j = 0; j < kGroups / 4; ++j) sum[j] = j == gi ? t : sum[j];
   }
   // the group sums, added in group order (the samples' LDS is done with)
   __syncthreads();

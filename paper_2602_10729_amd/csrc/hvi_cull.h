@@ -8,15 +8,21 @@
 // more than the terms do. Here the lanes test 64 boxes at a time instead: each
 // member's largest value per objective over the wave is reduced with DPP, lane
 // i compares box c0 + i's lower corner with it, and the ballots are one 64-bit
-// mask of the boxes that the member may reach. The waves then visit only those
-// boxes, in order, by which members reach them: one (its own extent product),
-// two (two products less their intersection), more (all 2^Q - 1 subsets).
-// Every term left out is exactly zero on every lane, and a lane adds the others
-// box after box whatever the way taken: which boxes and ways these are depends
-// on the batches that share the wave, a batch's sum does not. A box's corner and widths come
+// mask of the boxes that the member may reach. The boxes that one member reaches
+// are visited member by member for its own extent product; a box that two or
+// more reach ends a stretch of them and is visited for all its subsets' terms.
+// Every term left out is exactly zero on every lane. Each member's own products
+// and the larger subsets' terms have sums of their own (HviSums), and each sum
+// takes its boxes in order: which boxes are visited, and by which loop, depends
+// on the batches that share the wave, a batch's sums do not. (One sum, the
+// members chosen box by box, is as regular but pays for the branches: 33331
+// constrained pairs, 137 boxes, 300 samples 249 us against 184; members first,
+// then pairs, without regard to the order, 176.) A box's corner and widths come
 // through the scalar cache (its address is uniform) as scalar operands; the
 // visits are bound by scalar issue (mask and address), so one box at a time or
-// four measured 2-13% slower than two.
+// four measured 2-13% slower than two. The kernels that use this keep to 80
+// scalar registers: with more, only one of their workgroups of 16 waves fits a
+// CU (the same pairs: 254 us).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -43,30 +49,56 @@ __device__ __forceinline__ float wave_max(float v) {
 
 typedef const float __attribute__((address_space(4)))* const_floats;
 
+// Lower corner of box c, +inf (not reached) for c >= nbox.
+__device__ __forceinline__ void load_corner(const float* boxes, int nbox, int c, float (&l)[3]) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) l[k] = c < nbox ? boxes[6 * c + k] : __builtin_huge_valf();
+}
+
 // When a wave's lanes are far apart (candidates with spread-out means and small
 // variances) most boxes are marked and walking all of them in order is cheaper:
-// no masks, addresses that only count up, no test. A tested sample that cost
-// more than the walk lets the next kWalkSamples walk without a test (the lanes
-// stay as far apart as they are), and a front so small that the test alone
-// costs more is always walked. A walk adds the zeros that a visit leaves out,
-// nothing else changes. Issue costs in quarters of a box that one member
-// reaches: two members, all members (q = 4), the test, a box of the walk.
+// no masks, addresses that only count up. For q <= 2 that is decided for each
+// chunk of 64 from its masks (for q = 4 the second copy of the subsets' code in
+// that loop costs more than it gives). The test itself is saved, too, where it
+// keeps costing more than it saves: after two such samples in a row one is
+// walked without a test, after three 3, then 7, then 15 (a sample's reach
+// varies with its draw; 15 after the first such sample took 331 us for the
+// pairs above). A front so small that the test alone costs more is always
+// walked. A walk adds the zeros that a visit leaves out, nothing else changes.
+// Issue costs in quarters of a box that one member reaches: two members, all
+// members (q = 4), the test, a box of the walk.
 template <int Q>
 struct CullCost {
   static constexpr int kOwn = 4, kPair = 8, kAll = 28;
   static constexpr int kTest = Q == 1 ? 20 : Q == 2 ? 34 : 60;
   static constexpr int kWalk = Q == 1 ? 3 : Q == 2 ? 6 : 26;
 };
-constexpr int kWalkSamples = 15;
+
+// What a wave carries from sample to sample.
+struct CullState {
+  int skip = 0;     // samples to come that are walked without a test
+  int run = 0;      // 2^i - 1 after i tested samples in a row that cost more
+};
+
+// The sums of a lane's terms: each member's own extent products, the
+// intersections of three members, those of two and four.
+template <int Q>
+struct HviSums {
+  float own[Q] = {}, odd = 0.f, even = 0.f;
+  __device__ __forceinline__ float total() const {
+    float v = own[0];
+#pragma unroll
+    for (int a = 1; a < Q; ++a) v += own[a];
+    return Q > 2 ? (v + odd) - even : v - even;
+  }
+};
 
 // Terms of the boxes boxes[0 .. nbox) ([c][6]: lower corner, then widths; the
-// address is uniform) for the members' values y[a][k] of this lane, into pos
-// and neg (odd and even subsets). lo(c, k): lower corner k of box c, a vector
-// load by lane, +inf for c >= nbox. walk: samples to come that are walked
-// without a test (0 at first).
-template <int Q, typename Lo>
+// address is uniform) for the members' values y[a][k] of this lane, into h.
+// corner(c, l): lower corner of box c, vector loads by lane, +inf for c >= nbox.
+template <int Q, typename Corner>
 __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* boxes, int nbox,
-                                           Lo lo, int& walk, float& pos, float& neg) {
+                                           Corner corner, CullState& st, HviSums<Q>& h) {
   using Cost = CullCost<Q>;
   const const_floats bx = (const_floats)(uintptr_t)boxes;
   struct Box { float lo[3], w[3]; };
@@ -78,71 +110,68 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
 #pragma unroll
     for (int k = 0; k < 3; ++k) e[k] = __builtin_amdgcn_fmed3f(v[k] - b.lo[k], 0.0f, b.w[k]);
   };
-  auto own = [&](const float (&v)[3], const Box& b) {
+  auto own = [&](int a, const Box& b) {
     float e[3];
-    extents(v, b, e);
-    pos = fmaf(e[0] * e[1], e[2], pos);
+    extents(y[a], b, e);
+    h.own[a] = fmaf(e[0] * e[1], e[2], h.own[a]);
   };
-  auto pair = [&](const float (&v)[3], const float (&u)[3], const Box& b) {
+  auto pair = [&](int a, int d, const Box& b) {
     float e[3], f[3];
-    extents(v, b, e);
-    extents(u, b, f);
-    pos = fmaf(e[0] * e[1], e[2], pos);
-    pos = fmaf(f[0] * f[1], f[2], pos);
-    neg = fmaf(fminf(e[0], f[0]) * fminf(e[1], f[1]), fminf(e[2], f[2]), neg);
+    extents(y[a], b, e);
+    extents(y[d], b, f);
+    h.own[a] = fmaf(e[0] * e[1], e[2], h.own[a]);
+    h.own[d] = fmaf(f[0] * f[1], f[2], h.own[d]);
+    h.even = fmaf(fminf(e[0], f[0]) * fminf(e[1], f[1]), fminf(e[2], f[2]), h.even);
   };
   auto all = [&](const Box& b) {
-    if constexpr (Q == 1) {
-      own(y[0], b);
-    } else if constexpr (Q == 2) {
-      pair(y[0], y[1], b);
-    } else {
-      constexpr int NS = 1 << Q;
-      float ext[NS][3];
+    constexpr int NS = 1 << Q;
+    float ext[NS][3];
 #pragma unroll
-      for (int a = 0; a < Q; ++a) extents(y[a], b, ext[1 << a]);
+    for (int a = 0; a < Q; ++a) extents(y[a], b, ext[1 << a]);
 #pragma unroll
-      for (int mask = 1; mask < NS; ++mask) {
-        const int low = mask & (-mask);
-        if (mask != low) {
+    for (int mask = 1; mask < NS; ++mask) {
+      const int low = mask & (-mask);
+      if (mask != low) {
 #pragma unroll
-          for (int k = 0; k < 3; ++k) ext[mask][k] = fminf(ext[mask ^ low][k], ext[low][k]);
-        }
-        const float t = ext[mask][0] * ext[mask][1];
-        if (__builtin_popcount(mask) & 1) pos = fmaf(t, ext[mask][2], pos);
-        else neg = fmaf(t, ext[mask][2], neg);
+        for (int k = 0; k < 3; ++k) ext[mask][k] = fminf(ext[mask ^ low][k], ext[low][k]);
       }
+      float& sum = mask == low                       ? h.own[__builtin_ctz(mask)]
+                   : (__builtin_popcount(mask) & 1) ? h.odd
+                                                    : h.even;
+      sum = fmaf(ext[mask][0] * ext[mask][1], ext[mask][2], sum);
     }
   };
-
-  if (walk == 0) walk = (Cost::kTest >= Cost::kWalk * nbox) ? 1 : 0;
-  float top[Q][3];
-  if (walk == 0) {
-    // An infinite value times an extent of zero is NaN, so a box that a lane
-    // does not reach counts as well then: every box, whatever the lanes beside
-    // it hold. (Bits of floats: +inf is above every number.)
-    int largest = 0;
-#pragma unroll
-    for (int a = 0; a < Q; ++a)
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        top[a][k] = wave_max(y[a][k]);
-        largest = max(largest, __float_as_int(top[a][k]));
-      }
-    walk = largest >= 0x7f800000 ? 1 : 0;
-  }
-  if (walk > 0) {
-    --walk;
+  auto walk = [&](unsigned c, unsigned c1) {
 #pragma unroll(Q == 1 ? 4 : 2)
-    for (unsigned c = 0; c < (unsigned)nbox; ++c) all(box(c));
+    for (; c < c1; ++c) all(box(c));
+  };
+
+  if (st.skip > 0 || Cost::kTest >= Cost::kWalk * nbox) {
+    st.skip = max(st.skip - 1, 0);
+    walk(0, nbox);
+    return;
+  }
+  // An infinite value times an extent of zero is NaN, so a box that a lane
+  // does not reach counts as well then: every box, whatever the lanes beside
+  // it hold. (Bits of floats: +inf is above every number.)
+  float top[Q][3];
+  int largest = 0;
+#pragma unroll
+  for (int a = 0; a < Q; ++a)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      top[a][k] = wave_max(y[a][k]);
+      largest = max(largest, __float_as_int(top[a][k]));
+    }
+  if (largest >= 0x7f800000) {
+    walk(0, nbox);
     return;
   }
   const int lane = threadIdx.x & 63;
   int cost = Cost::kTest;
   for (int c0 = 0; c0 < nbox; c0 += 64) {
     float l[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) l[k] = lo(c0 + lane, k);
+    corner(c0 + lane, l);
     uint64_t m[Q], any = 0, two = 0, more = 0;
 #pragma unroll
     for (int a = 0; a < Q; ++a) {
@@ -152,47 +181,62 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
       two |= any & m[a];
       any |= m[a];
     }
-    cost += Cost::kOwn * __builtin_popcountll(any);
-    if (Q > 1) cost += (Cost::kPair - Cost::kOwn) * __builtin_popcountll(two);
-    if (Q > 2) cost += (Cost::kAll - Cost::kPair) * __builtin_popcountll(more);
-    // box i of the chunk, by the members that reach it
-    auto visit = [&](unsigned i, const Box& b) {
-      const uint64_t bit = 1ull << i;
-      if (Q == 1) {
-        own(y[0], b);
-      } else if (!(two & bit)) {
-        if (Q == 4 && ((m[Q - 1] | m[Q - 2]) & bit)) {
-          if (m[Q - 1] & bit) own(y[Q - 1], b);
-          else own(y[Q - 2], b);
-        } else {
-          if (m[Q > 1] & bit) own(y[Q > 1], b);
-          else own(y[0], b);
-        }
-      } else if (Q > 2 && !(more & bit)) {
-#pragma unroll
-        for (int a = 0; a < Q; ++a)
-#pragma unroll
-          for (int d = a + 1; d < Q; ++d)
-            if (m[a] & m[d] & bit) pair(y[a], y[d], b);
-      } else {
-        all(b);
+    int visits = Cost::kOwn * __builtin_popcountll(any);
+    if (Q > 1) visits += (Cost::kPair - Cost::kOwn) * __builtin_popcountll(two);
+    if (Q > 2) visits += (Cost::kAll - Cost::kPair) * __builtin_popcountll(more);
+    cost += visits;
+    if constexpr (Q <= 2) {
+      const int left = min(nbox - c0, 64);
+      if (visits >= Cost::kWalk * left) {
+        walk(c0, c0 + left);
+        continue;
+      }
+    }
+    // member a's boxes in r, two at a time (after an odd first one), both
+    // requested before either is used
+    auto visit = [&](uint64_t r, int a) {
+      if (__builtin_popcountll(r) & 1) {
+        own(a, box(c0 + __builtin_ctzll(r)));
+        r &= r - 1;
+      }
+      while (r != 0) {
+        const Box b0 = box(c0 + __builtin_ctzll(r));
+        r &= r - 1;
+        const Box b1 = box(c0 + __builtin_ctzll(r));
+        r &= r - 1;
+        __builtin_amdgcn_sched_barrier(0);
+        own(a, b0);
+        own(a, b1);
       }
     };
-    // two boxes at a time, so that one's corner is on its way while the other
-    // is used
-    uint64_t r = any;
-    while (r) {
-      const unsigned i0 = __builtin_ctzll(r);
-      r &= r - 1;
-      const bool second = r != 0;
-      const unsigned i1 = second ? __builtin_ctzll(r) : i0;
-      r &= r - 1;
-      const Box b0 = box(c0 + i0), b1 = box(c0 + i1);
-      visit(i0, b0);
-      if (second) visit(i1, b1);
+    if (two == 0) {
+#pragma unroll
+      for (int a = 0; a < Q; ++a) visit(m[a], a);
+    } else if constexpr (Q > 1) {
+      uint64_t past = 0;                             // boxes up to the last shared one
+      for (uint64_t r = two;; r &= r - 1) {
+        const uint64_t bit = r & (0 - r), below = r != 0 ? bit - 1 : ~0ull;
+        const uint64_t single = any & ~two & below & ~past;
+        if (single != 0)
+#pragma unroll
+          for (int a = 0; a < Q; ++a) visit(m[a] & single, a);
+        if (r == 0) break;
+        past = below | bit;
+        const Box b = box(c0 + __builtin_ctzll(r));
+        if (Q == 2 || (more & bit)) {
+          all(b);
+        } else {
+#pragma unroll
+          for (int a = 0; a < Q; ++a)
+#pragma unroll
+            for (int d = a + 1; d < Q; ++d)
+              if (m[a] & m[d] & bit) pair(a, d, b);
+        }
+      }
     }
   }
-  if (cost >= Cost::kWalk * nbox) walk = kWalkSamples;
+  st.run = cost >= Cost::kWalk * nbox ? min(2 * st.run + 1, 31) : 0;
+  st.skip = st.run >> 1;
 }
 
 }  // namespace

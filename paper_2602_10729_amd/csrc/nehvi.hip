@@ -1049,7 +1049,8 @@ __global__ __launch_bounds__(kET) void k_nehvi_ehvi(NehviEhviArgs a) {
 // by box in eight waves.
 constexpr int kGroups3 = 16;
 template <int Q, bool CONS>
-__global__ __launch_bounds__(1024) void k_nehvi_ehvi3(NehviEhviArgs a) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80)))
+void k_nehvi_ehvi3(NehviEhviArgs a) {
   extern __shared__ float esm[];
   constexpr int T = Q * (Q + 1) / 2;
   const int nt = blockDim.x, W = nt / 64;
@@ -1082,19 +1083,19 @@ __global__ __launch_bounds__(1024) void k_nehvi_ehvi3(NehviEhviArgs a) {
   const float* dp = a.D + bb * Q;
   const int64_t kstride = (int64_t)a.S * a.ldd;
   const int gs = (a.S + kGroups3 - 1) / kGroups3;   // draws per group
-  float sum[kGroups3 / 4];                          // this wave's groups (W >= 4)
-  int walk = 0;
+  float sum[kGroups3 / 4] = {};                     // this wave's groups (W >= 4)
+  CullState cull;
   auto load = [&](int s, float (&dv)[Q][3]) {
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
       for (int i = 0; i < Q; ++i) dv[i][k] = dp[k * kstride + (int64_t)s * a.ldd + i];
   };
-#pragma unroll
-  for (int gi = 0; gi < kGroups3 / 4; ++gi) {
+#pragma unroll 1                                    // one copy of the boxes' code
+  for (int gi = 0; gi < kGroups3 / W; ++gi) {
     const int g = wave * (kGroups3 / W) + gi;
-    const int s0 = g * gs, s1 = (gi < kGroups3 / W) ? min(a.S, s0 + gs) : s0;
-    float pos = 0.f, neg = 0.f;
+    const int s0 = g * gs, s1 = min(a.S, s0 + gs);
+    HviSums<Q> h;
     float dv[Q][3];
     if (s0 < s1) load(s0, dv);
     for (int s = s0; s < s1; ++s) {
@@ -1116,11 +1117,11 @@ __global__ __launch_bounds__(1024) void k_nehvi_ehvi3(NehviEhviArgs a) {
       const int o0 = __builtin_amdgcn_readfirstlane(off[s]);
       const int nbox = __builtin_amdgcn_readfirstlane(off[s + 1]) - o0;
       const float* bx = a.boxes + (int64_t)o0 * 6;
-      box_terms3<Q>(y, bx, nbox,
-                    [&](int c, int k) { return c < nbox ? bx[6 * c + k] : __builtin_huge_valf(); },
-                    walk, pos, neg);
+      box_terms3<Q>(y, bx, nbox, [&](int c, float (&l)[3]) { load_corner(bx, nbox, c, l); }, cull, h);
     }
-    sum[gi] = pos - neg;
+    const float t = h.total();
+#pragma unroll
+    for (int j = 0; j < kGroups3 / 4; ++j) sum[j] = j == gi ? t : sum[j];
   }
   __syncthreads();                      // the draws' LDS is done with
 #pragma unroll
