@@ -151,9 +151,11 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
     walk(0, nbox);
     return;
   }
-  // An infinite value times an extent of zero is NaN, so a box that a lane
-  // does not reach counts as well then: every box, whatever the lanes beside
-  // it hold. (Bits of floats: +inf is above every number.)
+  // An infinite value, or the product of two that overflows, times an extent of
+  // zero is NaN, so a box that a lane does not reach counts as well then: every
+  // box, whatever the lanes beside it hold. Below 2^62 no product of two extents
+  // overflows (the lower corners are observations' or the reference's values).
+  // Bits of floats: their order is the numbers'.
   float top[Q][3];
   int largest = 0;
 #pragma unroll
@@ -163,7 +165,7 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
       top[a][k] = wave_max(y[a][k]);
       largest = max(largest, __float_as_int(top[a][k]));
     }
-  if (largest >= 0x7f800000) {
+  if (largest >= 0x5e800000) {
     walk(0, nbox);
     return;
   }

@@ -164,15 +164,19 @@ def test_three_objective_batch_order(P, q, ls):
 
 
 @pytest.mark.parametrize("q", [1, 2, 4])
-def test_three_objective_infinite_samples(q):
-    """An infinite sample of one objective: its product with a box that the
-    batch does not reach is 0 * inf, so the value is NaN as it is box by box,
-    with any batches beside it and alone; the same for the noisy acquisition."""
+@pytest.mark.parametrize("big", [np.inf, 1e25])
+def test_three_objective_infinite_samples(q, big):
+    """An infinite sample of one objective, or samples of two whose product
+    overflows: the product with a box that the batch does not reach is 0 * inf,
+    so the value is NaN as it is box by box, with any batches beside it and
+    alone; the same for the noisy acquisition."""
     import torch
     import paper_2602_10729_amd as bo
-    _announce("infinite samples", q)
+    _announce("infinite samples", q, big)
     wl = _front_workload(12, q, 20, 100, seed=6)
-    wl.Z[7, 0, 1] = np.inf
+    wl.Z[7, 0, 1] = big
+    if np.isfinite(big):
+        wl.Z[7, 0, 0] = big
     full = gpu_run(wl)
     model, cand, Z = full["model"], to_dev(wl.cand), to_dev(wl.Z)
     one = [float(bo.score(model, cand[i:i + 1].contiguous(), wl.ref, Z)) for i in range(100)]
@@ -180,9 +184,9 @@ def test_three_objective_infinite_samples(q):
     if q == 1:
         lo, hi = bo.box_decomposition(wl.Y[full["front"]], wl.ref)
         y = full["mu"][:, 0] + full["sigma"][:, 0] * wl.Z[7, 0]              # [100, 3]
-        with np.errstate(invalid="ignore"):
-            ext = np.minimum(np.maximum(y[:, None] - lo, 0.0), hi - lo)
-            want = ext.prod(axis=2).sum(axis=1)
+        with np.errstate(invalid="ignore", over="ignore"):
+            ext = np.minimum(np.maximum(y[:, None] - lo, 0.0), hi - lo).astype(np.float32)
+            want = ((ext[..., 0] * ext[..., 1]) * ext[..., 2]).sum(axis=1)
         assert np.isnan(want).any()
         np.testing.assert_array_equal(np.isnan(full["ehvi"]), np.isnan(want))
     ZX = np.random.default_rng(9).standard_normal((20, 12, 3)).astype(np.float32)
