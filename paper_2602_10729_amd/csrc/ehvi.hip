@@ -69,9 +69,10 @@ __device__ __forceinline__ float mask_infeasible(const float (&y)[MO], const Ehv
 // S = 512: 78.4 -> 9.2 us; M = 65536, S = 256: 58.7 -> 26.9 us; M = 1048576,
 // S = 512 (W = 1 either way): 326 and 319 us.
 constexpr int kGroups = 16;
-template <int MO, int SC, bool CONS>
+template <int SC, bool CONS>
 __global__ __launch_bounds__(1024) void k_ehvi_q1(EhviArgs a, int W) {
   extern __shared__ float sm[];
+  constexpr int MO = 2;
   float* zs = sm;                                   // [S][MO]
   float* bx = sm + a.S * MO;                        // [nbox][2*MO]
   float* part = bx + a.nbox * 2 * MO;               // W > 1: [64 max(W, 4) / (64 W)][kGroups][64]
@@ -154,9 +155,10 @@ int q1_waves(int64_t nbat) {
 // a workgroup share its 64 batches and split the samples; their partial sums
 // are added in LDS in wave order.
 constexpr int kQWaves = kThreads / 64;
-template <int MO, int Q, int SC, bool CONS>
+template <int Q, int SC, bool CONS>
 __global__ __launch_bounds__(kThreads) void k_ehvi_q(EhviArgs a) {
   extern __shared__ float sm[];
+  constexpr int MO = 2;
   constexpr int T = Q * (Q + 1) / 2;
   constexpr int NS = (1 << Q);
   float* zs = sm;                                   // [S][Q][MO]
@@ -430,23 +432,22 @@ template <bool CONS>
 hipError_t launch_2(const EhviArgs& a, hipStream_t st) {
   const size_t lds = ehvi_lds_bytes(a.S, a.q, 2, a.nbox);
   if (a.q == 1) {
-    // the group sums of W > 1 waves come after the boxes; where they do not
-    // fit (thousands of samples and boxes) one wave takes all the groups
-    int W = q1_waves(a.nbat);
-    const size_t part = sizeof(float) * kGroups * 64 * (W < 4 ? 4 / W : 1);
-    if (lds + part > kLdsBytes) W = 1;
+    // the group sums of W > 1 waves come after the boxes (at most 4096 samples
+    // and 2049 boxes: 81 KiB in all)
+    const int W = q1_waves(a.nbat);
     const int per = 64 * (W < 4 ? 4 / W : 1);       // candidates per workgroup
+    const size_t part = W > 1 ? sizeof(float) * kGroups * per : 0;
+    if (lds + part > kLdsBytes) return hipErrorInvalidValue;
     const unsigned grid = static_cast<unsigned>((a.nbat + per - 1) / per);
-    return launch_k(&k_ehvi_q1<2, 16, CONS>, grid, 64 * std::max(W, 4), lds + (W > 1 ? part : 0),
-                    st, a, W);
+    return launch_k(&k_ehvi_q1<16, CONS>, grid, 64 * std::max(W, 4), lds + part, st, a, W);
   }
   // q > 1: a workgroup per 64 batches (LDS: at least the waves' partial sums,
   // which reuse the space at the end)
   const unsigned grid = static_cast<unsigned>((a.nbat + 63) / 64);
   const size_t ldsq = std::max<size_t>(lds, sizeof(float) * kThreads);
   switch (a.q) {
-    case 2: return launch_k(&k_ehvi_q<2, 2, 4, CONS>, grid, kThreads, ldsq, st, a);
-    case 4: return launch_k(&k_ehvi_q<2, 4, 2, CONS>, grid, kThreads, ldsq, st, a);
+    case 2: return launch_k(&k_ehvi_q<2, 4, CONS>, grid, kThreads, ldsq, st, a);
+    case 4: return launch_k(&k_ehvi_q<4, 2, CONS>, grid, kThreads, ldsq, st, a);
     default: return hipErrorInvalidValue;
   }
 }

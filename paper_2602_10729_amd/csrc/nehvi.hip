@@ -863,13 +863,14 @@ __device__ __forceinline__ float nz_mask(const float (&y)[MO], const NehviEhviAr
   return ok ? y[0] : -__builtin_inff();
 }
 
-template <int MO, int Q, bool CONS, bool LDSB>
+template <int Q, bool CONS, bool LDSB>
 __global__ __launch_bounds__(kET) void k_nehvi_ehvi(NehviEhviArgs a) {
   extern __shared__ float esm[];
+  constexpr int MO = 2;
   constexpr int BW = 2 * MO;
   constexpr int T = Q * (Q + 1) / 2;
   constexpr int NS = 1 << Q;
-  constexpr int U = (Q * MO <= 2) ? 16 : (Q * MO <= 4) ? 8 : (Q * MO <= 8) ? 4 : 2;
+  constexpr int U = Q == 1 ? 16 : Q == 2 ? 8 : 4;
   float* zs = esm;                                                  // [S][Q][MO]
   int* off = reinterpret_cast<int*>(zs + a.S * Q * MO);            // [S + 1]
   float* bxl = reinterpret_cast<float*>(off + a.S + 1);            // [total][BW] (LDSB)
@@ -960,15 +961,13 @@ __global__ __launch_bounds__(kET) void k_nehvi_ehvi(NehviEhviArgs a) {
           lo[k] = bx[c * BW + k];
           w[k] = bx[c * BW + MO + k];
         }
-        if constexpr (Q > 1 || MO > 2) {
+        if constexpr (Q > 1) {
           // a box whose lower corner no member exceeds in some objective adds
           // exactly zero; skip it when that holds on every lane
           bool nz = true;
 #pragma unroll
           for (int k = 0; k < MO; ++k) nz = nz && (ymax[k] > lo[k]);
           if (__ballot(nz) == 0) continue;
-        }
-        if constexpr (Q > 1) {
           // the members that reach the box (above its lower corner in every
           // objective) on some lane: when only one does, the box adds that
           // member's own extent product (the other subset terms are zeros)
@@ -1158,26 +1157,26 @@ hipError_t nz_ehvi3(const NehviEhviArgs& a, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-template <int MO, int Q, bool CONS>
+template <int Q, bool CONS>
 hipError_t nz_ehvi_launch(const NehviEhviArgs& a, bool ldsb, size_t lds, unsigned grid,
                           hipStream_t st) {
   // more than 64 KiB of dynamic LDS: opt in on every launch, so that it holds
   // on whichever device is current
-  const void* f = ldsb ? reinterpret_cast<const void*>(&k_nehvi_ehvi<MO, Q, CONS, true>)
-                       : reinterpret_cast<const void*>(&k_nehvi_ehvi<MO, Q, CONS, false>);
+  const void* f = ldsb ? reinterpret_cast<const void*>(&k_nehvi_ehvi<Q, CONS, true>)
+                       : reinterpret_cast<const void*>(&k_nehvi_ehvi<Q, CONS, false>);
   hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e != hipSuccess) return e;
-  if (ldsb) hipLaunchKernelGGL((k_nehvi_ehvi<MO, Q, CONS, true>), dim3(grid), dim3(kET), lds, st, a);
-  else hipLaunchKernelGGL((k_nehvi_ehvi<MO, Q, CONS, false>), dim3(grid), dim3(kET), lds, st, a);
+  if (ldsb) hipLaunchKernelGGL((k_nehvi_ehvi<Q, CONS, true>), dim3(grid), dim3(kET), lds, st, a);
+  else hipLaunchKernelGGL((k_nehvi_ehvi<Q, CONS, false>), dim3(grid), dim3(kET), lds, st, a);
   return hipGetLastError();
 }
 
-template <int MO, bool CONS>
+template <bool CONS>
 hipError_t nz_ehvi_q(const NehviEhviArgs& a, bool ldsb, size_t lds, unsigned grid, hipStream_t st) {
   switch (a.q) {
-    case 1: return nz_ehvi_launch<MO, 1, CONS>(a, ldsb, lds, grid, st);
-    case 2: return nz_ehvi_launch<MO, 2, CONS>(a, ldsb, lds, grid, st);
-    case 4: return nz_ehvi_launch<MO, 4, CONS>(a, ldsb, lds, grid, st);
+    case 1: return nz_ehvi_launch<1, CONS>(a, ldsb, lds, grid, st);
+    case 2: return nz_ehvi_launch<2, CONS>(a, ldsb, lds, grid, st);
+    case 4: return nz_ehvi_launch<4, CONS>(a, ldsb, lds, grid, st);
   }
   return hipErrorInvalidValue;
 }
@@ -1291,8 +1290,8 @@ hipError_t launch_nehvi_ehvi(const NehviEhviArgs& a, hipStream_t st) {
   // q = 1: a lane per batch; q > 1: a workgroup per 64 batches
   const int per = (a.q == 1) ? kET : 64;
   const unsigned grid = static_cast<unsigned>((a.nbat + per - 1) / per);
-  if (a.m == 2) return a.cons ? nz_ehvi_q<2, true>(a, ldsb, lds, grid, st)
-                              : nz_ehvi_q<2, false>(a, ldsb, lds, grid, st);
+  if (a.m == 2) return a.cons ? nz_ehvi_q<true>(a, ldsb, lds, grid, st)
+                              : nz_ehvi_q<false>(a, ldsb, lds, grid, st);
   return hipErrorInvalidValue;
 }
 
