@@ -105,36 +105,69 @@ def _front_workload(P, q, S, M, seed=0):
     return wl
 
 
-@pytest.mark.parametrize("P,q,S,near", [(1, 1, 1, False), (31, 1, 17, False), (32, 1, 15, True), (100, 1, 33, True),
-                                        (1, 2, 16, False), (33, 2, 33, False), (100, 2, 5, True),
-                                        (1, 4, 3, False), (21, 4, 31, True), (31, 4, 1, False), (32, 4, 16, False),
-                                        (64, 4, 9, False), (100, 4, 18, True)])
-def test_three_objective_box_culling(P, q, S, near):
+def _interval(ys, band, boxes, low, shift):
+    """Range of the acquisition of member draws ys [M, S, q, 3] that are each
+    known to +-band, against the boxes of each sample (boxes(s) -> lo, hi). A
+    member within band of a threshold counts in the upper bound only; with
+    shift the draws themselves are moved by band (the HVI grows with each)."""
+    d = ys - (-np.inf if low is None else np.asarray(low, np.float64))
+    sure, maybe = np.all(d > band, axis=-1).astype(float), np.all(d >= -band, axis=-1).astype(float)
+    b = band if shift else 0.0
+    lo = [O.qhvi((ys - b)[:, s], *boxes(s), sure[:, s]) for s in range(ys.shape[1])]
+    hi = [O.qhvi((ys + b)[:, s], *boxes(s), maybe[:, s]) for s in range(ys.shape[1])]
+    return np.mean(lo, axis=0), np.mean(hi, axis=0)
+
+
+@pytest.mark.parametrize("P,q,S,where", [(1, 1, 1, "far"), (31, 1, 17, "far"), (32, 1, 15, "near"),
+                                         (100, 1, 33, "near"), (1, 2, 16, "far"), (33, 2, 33, "far"),
+                                         (64, 2, 18, "apart"), (100, 2, 5, "near"), (1, 4, 3, "far"),
+                                         (21, 4, 31, "near"), (31, 4, 1, "far"), (32, 4, 16, "far"),
+                                         (40, 4, 17, "apart"), (64, 4, 9, "far"), (100, 4, 18, "near")])
+def test_three_objective_box_culling(P, q, S, where):
     """Boxes culled 64 at a time per wave: box counts either side of 64, sample
     groups with remainders and empty ones, a partial wave of batches, members
-    that share boxes, and (near: candidates by the observations, small
-    variances) waves whose lanes are far apart. Against the oracle."""
-    from gpu_util import oracle_fit, oracle_score
+    that share boxes, and waves whose lanes are far apart (apart: longer
+    lengthscales; near: candidates by the observations, small variances).
+    Against the oracle, every batch: plain at the parity bar, constrained between
+    the bounds that samples within the posterior's tolerance of a threshold
+    leave open (single points near the data: the acquisition stage on the GPU's
+    own posterior, whose samples both sides form within a few units of 2^-24)."""
+    from gpu_util import (NEAR_VAR_ULPS, assert_within_bounds, constrained_bounds, oracle_fit,
+                          oracle_score)
     wl = _front_workload(P, q, S, 70)
-    if near:
+    if where == "apart":
+        wl.lengthscale[:] = 0.8
+    if where == "near":
         wl.cand = bi.near_data_candidates(wl, 70, scale=0.02)
     lower = np.quantile(wl.Y, 0.2, axis=0).astype(np.float32)
-    for lo in (None, np.array([-np.inf, lower[1], -np.inf], np.float32)):
-        _announce("culled boxes", P, q, S, near, lo is not None)
+    om = oracle_fit(wl)
+    for lo in (None, np.array([-np.inf, lower[1], -np.inf], np.float32), lower):
+        _announce("culled boxes", P, q, S, where, lo)
         g = gpu_run(wl, lower=lo)
-        o = oracle_score(oracle_fit(wl), wl, lower=lo)
-        # near the data sigma is the noise level and the fp32 variance error
-        # absolute: the acquisition stage on the GPU's own posterior there
-        if near and q == 1 and lo is None:
-            want = oracle_ehvi_given(g["mu"], g["sigma"], wl.Z, o)
-        elif near or lo is not None:
-            # (samples at a threshold may flip; near data: the posterior's error)
-            ok = np.isclose(g["ehvi"], o["ehvi"], rtol=5e-3, atol=1e-5)
-            assert ok.mean() > 0.95
+        o = oracle_score(om, wl, lower=lo)
+        what = f"culled boxes, P={P} q={q} {where} {lo}"
+        if where == "near" and q > 1:
+            # mu at its bar; the covariance's error is absolute near the data, and
+            # an entry of its factor is off by at most the root of what the pivots
+            # collect of it (eight entries' errors)
+            C = O.chol_psd(o["cov"], 1.0)
+            Z = wl.Z.astype(np.float64)
+            ys = o["mu"][:, None] + np.einsum("ckab,sbk->csak", C, Z)
+            band = (1e-4 * np.abs(o["mu"][:, None]) + 1e-5 +
+                    np.sqrt(8 * NEAR_VAR_ULPS * 2.0 ** -24) * np.abs(Z).sum(axis=1)[None, :, None, :])
+            lb, ub = _interval(ys, band, lambda s: (o["lo"], o["hi"]), lo, True)
+            assert_within_bounds(g["ehvi"], lb, ub, TOL_EHVI, what)
+            assert np.isclose(g["ehvi"], o["ehvi"], rtol=5e-3, atol=1e-5).mean() > 0.95
             continue
+        if where == "near":
+            o = dict(o, mu=g["mu"].astype(np.float64), sigma=g["sigma"].astype(np.float64))
+            o["ehvi"] = oracle_ehvi_given(g["mu"], g["sigma"], wl.Z, o)
+        if lo is None:
+            np.testing.assert_allclose(g["ehvi"], o["ehvi"], rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
         else:
-            want = o["ehvi"]
-        np.testing.assert_allclose(g["ehvi"], want, rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
+            lb, ub = constrained_bounds(o, wl.Z, lo, safety=0.05 if where == "near" else 4.0)
+            assert_within_bounds(g["ehvi"], lb, ub, TOL_EHVI, what)
+            assert (lb == ub).mean() > 0.5, "few batches without an ambiguous sample"
 
 
 @pytest.mark.parametrize("P,q,ls", [(21, 1, 1.5), (1, 2, 0.3), (21, 2, 1.5), (100, 2, 0.3), (21, 4, 1.5), (100, 4, 0.3)])
@@ -238,19 +271,64 @@ def test_three_objective_samples_at_the_lds_limit():
 @pytest.mark.parametrize("q,S", [(1, 1), (1, 33), (2, 17), (4, 15), (4, 65)])
 def test_noisy_three_objective_draw_groups(q, S):
     """The noisy acquisition's culled boxes: draw groups with remainders and
-    empty ones, a partial wave of batches, every draw's own boxes."""
+    empty ones, a partial wave of batches, every draw's own boxes; with
+    thresholds between the bounds that draws within the posterior's tolerance
+    of one leave open (a factor's entries are at most sqrt(s) = 1)."""
     import torch
     import paper_2602_10729_amd as bo
-    from gpu_util import oracle_fit
-    _announce("noisy draw groups", q, S)
+    from gpu_util import assert_within_bounds, oracle_fit
     wl = _front_workload(60, q, S, 70, seed=2)
     ZX = np.random.default_rng(9).standard_normal((S, 60, 3)).astype(np.float32)
     model = bo.fit(to_dev(wl.X), to_dev(wl.Y), wl.lengthscale, wl.outputscale, wl.noise)
-    bo.nehvi_prepare(model, to_dev(ZX), wl.ref)
-    e = bo.score_nehvi(model, to_dev(wl.cand), to_dev(wl.Z)).cpu().numpy()
+    om = oracle_fit(wl)
+    cand = wl.cand.astype(np.float64)
     Zs = wl.Z[:, 0, :] if q == 1 else wl.Z
-    o = O.nehvi(oracle_fit(wl), wl.cand.astype(np.float64), wl.ref.astype(np.float64), ZX, Zs)
-    np.testing.assert_allclose(e, o["ehvi"], rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
+    lower = np.quantile(wl.Y, 0.2, axis=0).astype(np.float32)
+    for low in (None, lower):
+        _announce("noisy draw groups", q, S, low is not None)
+        bo.nehvi_prepare(model, to_dev(ZX), wl.ref, lower=low)
+        e = bo.score_nehvi(model, to_dev(wl.cand), to_dev(wl.Z)).cpu().numpy()
+        o = O.nehvi(om, cand, wl.ref.astype(np.float64), ZX, Zs, lower=low)
+        if low is None:
+            np.testing.assert_allclose(e, o["ehvi"], rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
+            continue
+        F, Ls = O.insample_samples(om, ZX.astype(np.float64))
+        Z64 = wl.Z.astype(np.float64)
+        if q == 1:
+            Kxx = [om.cov(k, om.X, om.X) for k in range(3)]
+            ys = O.candidate_samples(om, cand.reshape(70, -1), ZX.astype(np.float64), Z64[:, 0], Ls, Kxx)[:, :, None]
+        else:
+            ys = O.batch_samples(om, cand, ZX.astype(np.float64), Z64, Ls)
+        band = 4.0 * (1e-4 * np.abs(ys) + 1e-4 * np.abs(Z64).sum(axis=1)[None, :, None, :] + 1e-5)
+        lb, ub = _interval(ys, band, lambda s: o["boxes"][s], low, False)
+        assert_within_bounds(e, lb, ub, TOL_EHVI, f"noisy draw groups q={q} S={S}")
+
+
+@pytest.mark.parametrize("q", [1, 2, 4])
+def test_three_objective_wave_counts(q):
+    """16, 8 and 4 waves share 64 batches and the groups of samples by the number
+    of batches (lines at 1024 and 2048 sets of 64), plain and noisy: a batch's
+    value does not depend on it, and the first ones are the oracle's."""
+    import torch
+    import paper_2602_10729_amd as bo
+    from gpu_util import oracle_fit, oracle_score
+    wl = _front_workload(8, q, 19, 131100, seed=5)
+    om = oracle_fit(wl)
+    ZX = np.random.default_rng(9).standard_normal((19, 8, 3)).astype(np.float32)
+    model = bo.fit(to_dev(wl.X), to_dev(wl.Y), wl.lengthscale, wl.outputscale, wl.noise)
+    bo.nehvi_prepare(model, to_dev(ZX), wl.ref)
+    cand, Z = to_dev(wl.cand), to_dev(wl.Z)
+    Zs = wl.Z[:, 0, :] if q == 1 else wl.Z
+    plain = lambda c: bo.score(model, c, wl.ref, Z).cpu().numpy()
+    noisy = lambda c: bo.score_nehvi(model, c, Z).cpu().numpy()
+    want = (oracle_score(om, wl, cand=wl.cand[:64])["ehvi"],
+            O.nehvi(om, wl.cand[:64].astype(np.float64), wl.ref.astype(np.float64), ZX, Zs)["ehvi"])
+    for score, w, name in ((plain, want[0], "plain"), (noisy, want[1], "noisy")):
+        full = score(cand)
+        np.testing.assert_allclose(full[:64], w, rtol=TOL_EHVI[0], atol=TOL_EHVI[1])
+        for M in (64, 65472, 65473, 131008, 131009):
+            _announce("wave counts", q, name, M)
+            np.testing.assert_array_equal(score(cand[:M].contiguous()), full[:M])
 
 
 @pytest.mark.parametrize("M", [0, 1, 63, 1023, 1025, 16383, 16384, 16385])
