@@ -316,15 +316,14 @@ __global__ __launch_bounds__(kThreads) void k_ehvi_q(EhviArgs a) {
 // boxes are culled per wave (hvi_cull.h). Lanes past the batch sit at -inf.
 // Bound by vector and scalar issue. Against testing box after box in chunks of
 // 2 to 16 samples (the two-objective kernels' way): 131072 batches of 4, 512
-// samples, 235 boxes 10.40 -> 2.03 ms; 33331 pairs, 300 samples, 137 boxes,
+// samples, 235 boxes 10.40 -> 1.94 ms; 33331 pairs, 300 samples, 137 boxes,
 // constrained 1.14 -> 0.185 ms; 256 samples, 6 dimensions, lengthscales 0.3 and
 // 1.5 (the latter: small variances, candidates far apart), 145 boxes: 65536
 // single points 0.65 -> 0.50 and 0.65 -> 0.58 ms, 32768 pairs 1.33 -> 0.48 and
 // 1.36 -> 0.53, 16384 batches of 4 2.93 -> 0.88 and 3.05 -> 1.06; 3 boxes 51 -> 29
-// and 49 -> 28 us, 36 -> 22 and 39 -> 22, 68 -> 58 and 79 -> 61.
+// and 49 -> 28 us, 36 -> 22 and 39 -> 22, 68 -> 55 and 79 -> 59.
 template <int Q, bool CONS>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80)))
-void k_ehvi3(EhviArgs a, bool lds_lo) {
+__device__ __forceinline__ void ehvi3(const EhviArgs& a, bool lds_lo) {
   extern __shared__ float sm[];
   constexpr int T = Q * (Q + 1) / 2;
   const int nt = blockDim.x, W = nt / 64;
@@ -408,6 +407,15 @@ void k_ehvi3(EhviArgs a, bool lds_lo) {
   if (valid) a.ehvi[b] = nan_in ? __builtin_nanf("") : tot / static_cast<float>(a.S);
 }
 
+template <int Q, bool CONS>
+__global__ __launch_bounds__(1024) BO_CULL_SGPRS void k_ehvi3(EhviArgs a, bool lds_lo) {
+  ehvi3<Q, CONS>(a, lds_lo);
+}
+template <bool CONS>
+__global__ __launch_bounds__(1024) void k_ehvi3_q4(EhviArgs a, bool lds_lo) {
+  ehvi3<4, CONS>(a, lds_lo);
+}
+
 // Waves per 64 batches with three objectives: eight waves a SIMD for a full
 // chip, at most one per sample group.
 int waves3(int64_t nbat) {
@@ -464,7 +472,7 @@ hipError_t launch_3(const EhviArgs& a, hipStream_t st) {
   switch (a.q) {
     case 1: return launch_k(&k_ehvi3<1, CONS>, grid, threads, lds, st, a, lds_lo);
     case 2: return launch_k(&k_ehvi3<2, CONS>, grid, threads, lds, st, a, lds_lo);
-    case 4: return launch_k(&k_ehvi3<4, CONS>, grid, threads, lds, st, a, lds_lo);
+    case 4: return launch_k(&k_ehvi3_q4<CONS>, grid, threads, lds, st, a, lds_lo);
     default: return hipErrorInvalidValue;
   }
 }

@@ -20,14 +20,17 @@
 // then pairs, without regard to the order, 176.) A box's corner and widths come
 // through the scalar cache (its address is uniform) as scalar operands; the
 // visits are bound by scalar issue (mask and address), so one box at a time or
-// four measured 2-13% slower than two. The kernels that use this keep to 80
-// scalar registers: with more, only one of their workgroups of 16 waves fits a
-// CU (the same pairs: 254 us).
+// four measured 2-13% slower than two.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+
+// The kernels with q = 1 and 2 keep to 80 scalar registers: with more, only one
+// of their workgroups of 16 waves fits a CU instead of two (the pairs above: 254
+// us against 184). With q = 4 the vector registers leave room for one anyway.
+#define BO_CULL_SGPRS __attribute__((amdgpu_num_sgpr(80)))
 
 namespace bo {
 namespace {

@@ -1044,12 +1044,11 @@ __global__ __launch_bounds__(kET) void k_nehvi_ehvi(NehviEhviArgs a) {
 // depend on W). A draw's boxes are culled per wave (hvi_cull.h): the lanes load
 // 64 lower corners at a time; the conditional means of the next draw are
 // requested before the current one's boxes are visited. 8192 batches of 4, 512
-// draws of 287 boxes (2048 observations): 3.88 -> 0.345 ms against a test box
+// draws of 287 boxes (2048 observations): 3.88 -> 0.364 ms against a test box
 // by box in eight waves.
 constexpr int kGroups3 = 16;
 template <int Q, bool CONS>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80)))
-void k_nehvi_ehvi3(NehviEhviArgs a) {
+__device__ __forceinline__ void nehvi_ehvi3(const NehviEhviArgs& a) {
   extern __shared__ float esm[];
   constexpr int T = Q * (Q + 1) / 2;
   const int nt = blockDim.x, W = nt / 64;
@@ -1133,6 +1132,15 @@ void k_nehvi_ehvi3(NehviEhviArgs a) {
   if (valid) a.ehvi[b] = nan_in ? __builtin_nanf("") : tot / static_cast<float>(a.S);
 }
 
+template <int Q, bool CONS>
+__global__ __launch_bounds__(1024) BO_CULL_SGPRS void k_nehvi_ehvi3(NehviEhviArgs a) {
+  nehvi_ehvi3<Q, CONS>(a);
+}
+template <bool CONS>
+__global__ __launch_bounds__(1024) void k_nehvi_ehvi3_q4(NehviEhviArgs a) {
+  nehvi_ehvi3<4, CONS>(a);
+}
+
 template <bool CONS>
 hipError_t nz_ehvi3(const NehviEhviArgs& a, hipStream_t st) {
   // eight waves a SIMD for a full chip, at most one per group of draws
@@ -1152,7 +1160,7 @@ hipError_t nz_ehvi3(const NehviEhviArgs& a, hipStream_t st) {
   switch (a.q) {
     case 1: return go(&k_nehvi_ehvi3<1, CONS>);
     case 2: return go(&k_nehvi_ehvi3<2, CONS>);
-    case 4: return go(&k_nehvi_ehvi3<4, CONS>);
+    case 4: return go(&k_nehvi_ehvi3_q4<CONS>);
   }
   return hipErrorInvalidValue;
 }

@@ -510,8 +510,12 @@ __device__ __forceinline__ void step(const Ctx& C, const PosteriorArgs& a, Produ
   if constexpr (LO >= RB) load_b<NT>(C, J + 1, 0, B0);
   if constexpr (PROD) {
     // interleave: the scheduler otherwise runs the producer's VALU work and
-    // the MFMAs as two separate stretches, and the two waves of a SIMD
-    // (kept in step by the barriers) then contend for the same unit
+    // the MFMAs as two separate stretches, and the two waves of a SIMD then
+    // contend for the same unit whenever they meet in one of them. nV per nM
+    // vector instructions follow an MFMA, about twice as many as there are (44
+    // per step, composite 80), so that they end in the step's first half: paced
+    // over all of it a plain launch took 0.5% longer, three times as many 0.3%;
+    // composite launches differ by less than 0.5%
     constexpr int nM = 3 * NCB * (RB - LO);
     constexpr int nV = 4 * (COMP ? 40 : 22);
     if constexpr (nM > 0) {
