@@ -10,17 +10,19 @@
 // i compares box c0 + i's lower corner with it, and the ballots are one 64-bit
 // mask of the boxes that the member may reach. The boxes that one member reaches
 // are visited member by member for its own extent product; a box that two or
-// more reach ends a stretch of them and is visited for all its subsets' terms.
-// Every term left out is exactly zero on every lane. Each member's own products
-// and the larger subsets' terms have sums of their own (HviSums), and each sum
-// takes its boxes in order: which boxes are visited, and by which loop, depends
-// on the batches that share the wave, a batch's sums do not. (One sum, the
-// members chosen box by box, is as regular but pays for the branches: 33331
-// constrained pairs, 137 boxes, 300 samples 249 us against 184; members first,
-// then pairs, without regard to the order, 176.) A box's corner and widths come
-// through the scalar cache (its address is uniform) as scalar operands; the
-// visits are bound by scalar issue (mask and address), so one box at a time or
-// four measured 2-13% slower than two.
+// more reach is visited for all its subsets' terms, after those before it of its
+// members. Every term left out is exactly zero on every lane. Each member's own
+// products and the larger subsets' terms have sums of their own (HviSums), and
+// each sum takes its boxes in order: which boxes are visited, and by which loop,
+// depends on the batches that share the wave, a batch's sums do not. What that
+// order costs: 33331 constrained pairs, 137 boxes, 300 samples 176 us where all
+// single boxes went first, then pairs, 184 now (one sum, the members chosen box
+// by box: 249); 32768 batches of 4, 279 boxes, 512 samples 0.68 -> 0.82 ms (50
+// boxes reached a sample, 5 by two members), with a composite model 2.06 -> 3.4
+// (173 reached, 54 by two, 20 by more; a test box by box 5.9 and 10.2). A box's
+// corner and widths come through the scalar cache (its address is uniform) as
+// scalar operands; the visits are bound by scalar issue (mask and address), so
+// one box at a time or four measured 2-13% slower than two.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -218,26 +220,38 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
 #pragma unroll
       for (int a = 0; a < Q; ++a) visit(m[a], a);
     } else if constexpr (Q > 1) {
-      uint64_t past = 0;                             // boxes up to the last shared one
-      for (uint64_t r = two;; r &= r - 1) {
-        const uint64_t bit = r & (0 - r), below = r != 0 ? bit - 1 : ~0ull;
-        const uint64_t single = any & ~two & below & ~past;
-        if (single != 0)
+      // a shared box waits for the boxes before it of its own members only
+      uint64_t left[Q];                              // single boxes to come
 #pragma unroll
-          for (int a = 0; a < Q; ++a) visit(m[a] & single, a);
-        if (r == 0) break;
-        past = below | bit;
+      for (int a = 0; a < Q; ++a) left[a] = m[a] & ~two;
+      for (uint64_t r = two; r != 0; r &= r - 1) {
+        const uint64_t bit = r & (0 - r);
         const Box b = box(c0 + __builtin_ctzll(r));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 0; a < Q; ++a)
+          if (Q == 2 || (m[a] & bit)) {
+            const uint64_t now = left[a] & (bit - 1);
+            if (now != 0) {
+              visit(now, a);
+              left[a] &= ~now;
+            }
+          }
         if (Q == 2 || (more & bit)) {
           all(b);
+        } else if (m[0] & bit) {
+          if (m[1] & bit) pair(0, 1, b);
+          else if (m[Q - 2] & bit) pair(0, Q - 2, b);
+          else pair(0, Q - 1, b);
+        } else if (m[1] & bit) {
+          if (m[Q - 2] & bit) pair(1, Q - 2, b);
+          else pair(1, Q - 1, b);
         } else {
-#pragma unroll
-          for (int a = 0; a < Q; ++a)
-#pragma unroll
-            for (int d = a + 1; d < Q; ++d)
-              if (m[a] & m[d] & bit) pair(a, d, b);
+          pair(Q - 2, Q - 1, b);
         }
       }
+#pragma unroll
+      for (int a = 0; a < Q; ++a) visit(left[a], a);
     }
   }
   st.run = cost >= Cost::kWalk * nbox ? min(2 * st.run + 1, 31) : 0;
