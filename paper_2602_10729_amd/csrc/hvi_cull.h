@@ -105,10 +105,12 @@ template <int Q, typename Corner>
 __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* boxes, int nbox,
                                            Corner corner, CullState& st, HviSums<Q>& h) {
   using Cost = CullCost<Q>;
-  const const_floats bx = (const_floats)(uintptr_t)boxes;
+  typedef const char __attribute__((address_space(4)))* const_bytes;
+  const const_bytes bx = (const_bytes)(uintptr_t)boxes;
   struct Box { float lo[3], w[3]; };
   auto box = [&](unsigned c) {
-    const const_floats p = bx + 6u * c;
+    // (a 32-bit offset in bytes: the load adds it to the base itself)
+    const const_floats p = (const_floats)(bx + 24u * c);
     return Box{{p[0], p[1], p[2]}, {p[3], p[4], p[5]}};
   };
   auto extents = [&](const float (&v)[3], const Box& b, float (&e)[3]) {
