@@ -316,12 +316,12 @@ __global__ __launch_bounds__(kThreads) void k_ehvi_q(EhviArgs a) {
 // boxes are culled per wave (hvi_cull.h). Lanes past the batch sit at -inf.
 // Bound by vector and scalar issue. Against testing box after box in chunks of
 // 2 to 16 samples (the two-objective kernels' way): 131072 batches of 4, 512
-// samples, 235 boxes 10.40 -> 1.94 ms; 33331 pairs, 300 samples, 137 boxes,
-// constrained 1.14 -> 0.185 ms; 256 samples, 6 dimensions, lengthscales 0.3 and
+// samples, 235 boxes 10.40 -> 1.79 ms; 33331 pairs, 300 samples, 137 boxes,
+// constrained 1.14 -> 0.163 ms; 256 samples, 6 dimensions, lengthscales 0.3 and
 // 1.5 (the latter: small variances, candidates far apart), 145 boxes: 65536
-// single points 0.65 -> 0.50 and 0.65 -> 0.58 ms, 32768 pairs 1.33 -> 0.48 and
-// 1.36 -> 0.53, 16384 batches of 4 2.93 -> 0.88 and 3.05 -> 1.06; 3 boxes 51 -> 29
-// and 49 -> 28 us, 36 -> 22 and 39 -> 22, 68 -> 55 and 79 -> 59.
+// single points 0.65 -> 0.38 and 0.65 -> 0.46 ms, 32768 pairs 1.33 -> 0.40 and
+// 1.36 -> 0.52, 16384 batches of 4 2.93 -> 0.89 and 3.05 -> 1.06; 3 boxes 51 -> 29
+// and 49 -> 27 us, 36 -> 21 and 39 -> 21, 68 -> 55 and 79 -> 60.
 template <int Q, bool CONS>
 __device__ __forceinline__ void ehvi3(const EhviArgs& a, bool lds_lo) {
   extern __shared__ float sm[];

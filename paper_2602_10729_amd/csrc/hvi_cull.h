@@ -15,14 +15,16 @@
 // products and the larger subsets' terms have sums of their own (HviSums), and
 // each sum takes its boxes in order: which boxes are visited, and by which loop,
 // depends on the batches that share the wave, a batch's sums do not. What that
-// order costs: 33331 constrained pairs, 137 boxes, 300 samples 176 us where all
-// single boxes went first, then pairs, 184 now (one sum, the members chosen box
-// by box: 249); 32768 batches of 4, 279 boxes, 512 samples 0.68 -> 0.82 ms (50
-// boxes reached a sample, 5 by two members), with a composite model 2.06 -> 3.4
-// (173 reached, 54 by two, 20 by more; a test box by box 5.9 and 10.2). A box's
-// corner and widths come through the scalar cache (its address is uniform) as
-// scalar operands; the visits are bound by scalar issue (mask and address), so
-// one box at a time or four measured 2-13% slower than two.
+// order costs: where single boxes went first, then pairs, 32768 batches of 4,
+// 279 boxes, 512 samples took 0.68 ms, now 0.72 (50 boxes reached a sample, 5 by
+// two members), with a composite model 2.1, now 3.1 (173 reached, 54 by two, 20
+// by more; a test box by box 5.9 and 10.2). One sum, the members chosen box by
+// box, is slower by its branches (33331 constrained pairs, 137 boxes, 300 samples
+// 249 us when these loops took 184). A box's corner and widths come through the
+// scalar cache (its address is uniform) as scalar operands; the visits are bound
+// by scalar issue (mask and address), so the address is a 32-bit offset in bytes,
+// which the load adds itself (the pairs: 184 -> 164 us), and one box at a time or
+// four measured 2-13% slower than two.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -31,7 +33,7 @@
 
 // The kernels with q = 1 and 2 keep to 80 scalar registers: with more, only one
 // of their workgroups of 16 waves fits a CU instead of two (the pairs above: 254
-// us against 184). With q = 4 the vector registers leave room for one anyway.
+// us against 184 then). With q = 4 the vector registers leave room for one anyway.
 #define BO_CULL_SGPRS __attribute__((amdgpu_num_sgpr(80)))
 
 namespace bo {
@@ -227,26 +229,28 @@ __device__ __forceinline__ void box_terms3(const float (&y)[Q][3], const float* 
 #pragma unroll
       for (int a = 0; a < Q; ++a) left[a] = m[a] & ~two;
       for (uint64_t r = two; r != 0; r &= r - 1) {
-        const uint64_t bit = r & (0 - r);
-        const Box b = box(c0 + __builtin_ctzll(r));
+        const unsigned i = __builtin_ctzll(r);
+        const uint64_t below = (1ull << i) - 1;
+        auto in = [&](uint64_t mask) { return (mask >> i) & 1; };
+        const Box b = box(c0 + i);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int a = 0; a < Q; ++a)
-          if (Q == 2 || (m[a] & bit)) {
-            const uint64_t now = left[a] & (bit - 1);
+          if (Q == 2 || in(m[a])) {
+            const uint64_t now = left[a] & below;
             if (now != 0) {
               visit(now, a);
               left[a] &= ~now;
             }
           }
-        if (Q == 2 || (more & bit)) {
+        if (Q == 2 || in(more)) {
           all(b);
-        } else if (m[0] & bit) {
-          if (m[1] & bit) pair(0, 1, b);
-          else if (m[Q - 2] & bit) pair(0, Q - 2, b);
+        } else if (in(m[0])) {
+          if (in(m[1])) pair(0, 1, b);
+          else if (in(m[Q - 2])) pair(0, Q - 2, b);
           else pair(0, Q - 1, b);
-        } else if (m[1] & bit) {
-          if (m[Q - 2] & bit) pair(1, Q - 2, b);
+        } else if (in(m[1])) {
+          if (in(m[Q - 2])) pair(1, Q - 2, b);
           else pair(1, Q - 1, b);
         } else {
           pair(Q - 2, Q - 1, b);

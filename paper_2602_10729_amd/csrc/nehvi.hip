@@ -1044,7 +1044,7 @@ __global__ __launch_bounds__(kET) void k_nehvi_ehvi(NehviEhviArgs a) {
 // depend on W). A draw's boxes are culled per wave (hvi_cull.h): the lanes load
 // 64 lower corners at a time; the conditional means of the next draw are
 // requested before the current one's boxes are visited. 8192 batches of 4, 512
-// draws of 287 boxes (2048 observations): 3.88 -> 0.364 ms against a test box
+// draws of 287 boxes (2048 observations): 3.88 -> 0.342 ms against a test box
 // by box in eight waves.
 constexpr int kGroups3 = 16;
 template <int Q, bool CONS>
